@@ -185,8 +185,8 @@ int mad_draft_step_attn(const void *q, int B, int Hq, int Hkv, int d, int dtype,
  *   mem    linear view to append to; requires mem.len[b] + n_new <= mem.cap
  * B * n_new <= MAD_MAX_UPDATE_ROWS; D a multiple of 64; d in {64, 128}.
  * BF16 runs the projection as a weight stream (at most 8 rows) or on the
- * matrix cores; F32 on the vector ALUs.  No workspace: every output element is
- * produced by one workgroup.
+ * matrix cores; F32 on the matrix cores in full fp32.  No workspace: every
+ * output element is produced by one workgroup.
  * Errors: MAD_EINVAL (null pointers, B, n_new, D, Hkv, rope_base <= 1 or not
  * finite, a firing sequence's len + n_new above cap), MAD_ENOTSUP (d, dtype).
  */

@@ -24,7 +24,8 @@
 // does not give; when the whole width fits LDS at once they are loaded
 // straight into it (global_load_lds_dwordx4) and the products follow them
 // block by block.
-// F32: a vector-ALU kernel, one thread per (row, rotation pair).
+// F32: the matrix cores in full fp32 (v_mfma_f32_4x4x1_16b_f32), four output
+// features per workgroup over the whole input width (update_f32_kernel).
 #include "mad_device.h"
 #include "mad_internal.h"
 
@@ -318,35 +319,88 @@ __global__ __launch_bounds__(256) void update_gemv_kernel(const UpdateArgs a) {
     }
 }
 
-// fp32: one thread per (row r, head h of K or V, feature pair j).
-__global__ __launch_bounds__(256) void update_f32_kernel(const UpdateArgs a) {
-    const int d = a.d, half = d / 2;
-    const int NH = 2 * a.Hkv;
-    const int total = a.R * NH * half;
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= total) return;
-    const int j = idx % half, hb = (idx / half) % NH, r = idx / (half * NH);
-    const float *x = reinterpret_cast<const float *>(a.x) + (size_t)r * a.D;
-    const float *w0 = reinterpret_cast<const float *>(a.w) + ((size_t)hb * d + j) * a.D;
-    const float *w1 = w0 + (size_t)half * a.D;
-    float y0 = 0.f, y1 = 0.f;
-    for (int k = 0; k < a.D; k += 4) {
-        const float4 xv = *reinterpret_cast<const float4 *>(x + k);
-        const float4 a0 = *reinterpret_cast<const float4 *>(w0 + k);
-        const float4 a1 = *reinterpret_cast<const float4 *>(w1 + k);
-        y0 = fmaf(xv.x, a0.x, y0); y0 = fmaf(xv.y, a0.y, y0); y0 = fmaf(xv.z, a0.z, y0); y0 = fmaf(xv.w, a0.w, y0);
-        y1 = fmaf(xv.x, a1.x, y1); y1 = fmaf(xv.y, a1.y, y1); y1 = fmaf(xv.z, a1.z, y1); y1 = fmaf(xv.w, a1.w, y1);
+// fp32: workgroup (fb, rt) owns two rotate-half pairs (four output features) of
+// one K or V head for up to 4 RG slot rows, over the whole input width.  The
+// weight rows are read once by the whole launch and are the bytes that bound it
+// (8.4 MB at 8 KV heads, d 64, D 2048), so the pass needs every CU loading:
+// 2 Hkv d / 4 workgroups, against 32 of one-thread-per-pair loops before.  The
+// products run on the matrix cores at full fp32 (v_mfma_f32_4x4x1_16b_f32): its
+// sixteen independent 4 x 4 blocks each take one k, so a 4-feature tile keeps
+// the full matrix rate (a 16 x 16 tile would leave 64 workgroups) and a wave
+// load is 256 contiguous bytes of each of four rows.  Block b of the wave's
+// k-step t holds k = 64 t + 4 b .. + 3, one product per element; the sixteen
+// blocks' sums are added across lanes once at the end, the waves' in LDS.
+// Measured at 16 rows, D 2048: 8.4 us, against 149 us before.
+template <int RG>
+__global__ __launch_bounds__(512) void update_f32_kernel(const UpdateArgs a) {
+    constexpr int NW = 8, U = 4;   // waves; k-steps whose loads are issued together
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int d = a.d, hd = d / 2, R = a.R, D = a.D;
+    const int q0 = 2 * blockIdx.x, hb = q0 / hd, j0 = q0 % hd;   // first pair: head hb, offset j0 (even)
+    const int r0 = blockIdx.y * 4 * RG;
+    __shared__ float s_red[NW][4][4 * RG];
+
+    // thread t < 8 RG finishes pair t % 2 of row t / 2; its angle is taken while the loads are in flight
+    const int er = r0 + (tid >> 1), ep = tid & 1, e_b = min(er, R - 1) / a.n_new;
+    const bool is_k = hb < a.Hkv, fin = tid < 8 * RG && er < R;
+
+    const int i4 = lane & 3, kb = (lane >> 2) * 4;   // feature / row within a 4-group, first k of the block
+    const float *w = reinterpret_cast<const float *>(a.w) + (size_t)(hb * d + j0 + (i4 & 1) + (i4 >> 1) * hd) * D + kb;
+    const float *x[RG];
+    #pragma unroll
+    for (int g = 0; g < RG; ++g)   // rows past R repeat the last row (never stored)
+        x[g] = reinterpret_cast<const float *>(a.x) + (size_t)min(r0 + 4 * g + i4, R - 1) * D + kb;
+    f32x4_v acc[RG];
+    #pragma unroll
+    for (int g = 0; g < RG; ++g) acc[g] = f32x4_v{0.f, 0.f, 0.f, 0.f};
+
+    const int nst = D >> 6;   // 64-wide k-steps; wave w takes w, w + NW, ...
+    float rc = 1.f, rs = 0.f;
+    for (int t0 = wave; t0 < nst; t0 += NW * U) {
+        f32x4_v wv[U], xv[U][RG];
+        #pragma unroll
+        for (int u = 0; u < U; ++u) {   // unconditional loads: a step past the end reads the last one, unused
+            const int k = min(t0 + NW * u, nst - 1) * 64;
+            wv[u] = *reinterpret_cast<const f32x4_v *>(w + k);
+            #pragma unroll
+            for (int g = 0; g < RG; ++g) xv[u][g] = *reinterpret_cast<const f32x4_v *>(x[g] + k);
+        }
+        if (t0 == wave && fin && is_k)
+            rope_cs(a.pos[er], rope_theta(j0 + ep, d, a.log2_base), &rc, &rs);
+        #pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (t0 + NW * u >= nst) break;
+            #pragma unroll
+            for (int e = 0; e < 4; ++e)
+                #pragma unroll
+                for (int g = 0; g < RG; ++g)
+                    acc[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(wv[u][e], xv[u][g][e], acc[g], 0, 0, 0);
+        }
     }
-    const int b = r / a.n_new, i = r - b * a.n_new;
-    if (!a.fire[b]) return;
-    const bool is_k = hb < a.Hkv;
-    const int h = is_k ? hb : hb - a.Hkv;
-    float o0 = y0, o1 = y1;
-    if (is_k) rope_rotate(y0, y1, a.pos[r], rope_theta(j, d, a.log2_base), &o0, &o1);
-    float *dst = reinterpret_cast<float *>(is_k ? a.mk : a.mv) + (size_t)b * a.m_seq + (size_t)h * a.m_head +
-                 (size_t)(a.mlen[b] + i) * d;
-    dst[j] = o0;
-    dst[j + half] = o1;
+    // lane 4 b + j holds, for block b, features 0 .. 3 (elements) of row j of each group: add the blocks
+    #pragma unroll
+    for (int g = 0; g < RG; ++g)
+        #pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float v = acc[g][e];
+            v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xF, 0xF, true));   // row_ror:8
+            v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x124, 0xF, 0xF, true));   // row_ror:4
+            v = pair_sum<32>(pair_sum<16>(v));
+            if (lane < 4) s_red[wave][e][4 * g + lane] = v;
+        }
+    __syncthreads();
+    if (!fin || !a.fire[e_b]) return;
+    float y0 = 0.f, y1 = 0.f;
+    #pragma unroll
+    for (int wv = 0; wv < NW; ++wv) {
+        y0 += s_red[wv][ep][er - r0];
+        y1 += s_red[wv][ep + 2][er - r0];
+    }
+    if (is_k) rope_apply(y0, y1, rc, rs, &y0, &y1);
+    float *dst = reinterpret_cast<float *>(is_k ? a.mk : a.mv) + (size_t)e_b * a.m_seq +
+                 (size_t)(is_k ? hb : hb - a.Hkv) * a.m_head + (size_t)(a.mlen[e_b] + er - e_b * a.n_new) * d;
+    dst[j0 + ep] = y0;
+    dst[j0 + ep + hd] = y1;
 }
 
 // ------------------------------------------------------------------ host ----
@@ -385,9 +439,15 @@ hipError_t launch_update(const UpdateArgs &a, int dtype, hipStream_t st) {
         else
             hipLaunchKernelGGL((update_rows_kernel<16, false>), grid, dim3(1024), 0, st, a);
     } else {
-        const int total = a.R * 2 * a.Hkv * (a.d / 2);
-        dim3 grid((unsigned)((total + 255) / 256)), block(256);
-        hipLaunchKernelGGL(update_f32_kernel, grid, block, 0, st, a);
+        // up to 16 rows share one read of the weight rows; more rows take more
+        // row tiles, whose weight reads hit L2
+        const unsigned fb = (unsigned)(2 * a.Hkv * a.d / 4);
+        if (a.R <= 4)
+            hipLaunchKernelGGL((update_f32_kernel<1>), dim3(fb), dim3(512), 0, st, a);
+        else if (a.R <= 8)
+            hipLaunchKernelGGL((update_f32_kernel<2>), dim3(fb), dim3(512), 0, st, a);
+        else
+            hipLaunchKernelGGL((update_f32_kernel<4>), dim3(fb, (unsigned)((a.R + 15) / 16)), dim3(512), 0, st, a);
     }
     return hipGetLastError();
 }

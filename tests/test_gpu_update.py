@@ -133,3 +133,16 @@ def test_matrix_core_kernel_input_widths(D, Hkv, d):
     rng = np.random.default_rng(D)
     pos = [[int(p) + 16 * i for i in range(6)] for p in rng.integers(100, 60000, 3)]
     _case(torch.bfloat16, 3, 6, D, Hkv, d, [5, 0, 17], 32, pos, fire=[1, 1, 0], seed=30 + D // 64)
+
+
+@pytest.mark.parametrize("B,n_new,D,Hkv,d", [(1, 1, 64, 1, 64), (1, 5, 192, 3, 64), (2, 4, 2048, 8, 64), (3, 3, 4160, 2, 128),
+                                             (9, 2, 1536, 4, 64), (16, 4, 2048, 8, 128)])
+def test_fp32_row_groups_and_widths(B, n_new, D, Hkv, d):
+    # the fp32 kernel's row groups (at most 4, 8, 16 rows; several 16-row tiles, the last one partial) and its
+    # k loop: fewer 64-wide steps than waves (D 64, 192), a partial batch of steps (1536) and a second batch (4160)
+    rng = np.random.default_rng(D + B)
+    pos = [[int(p) + 16 * i for i in range(n_new)] for p in rng.integers(1, 60000, B)]
+    fire = [1] * B
+    if B > 1:
+        fire[1] = 0
+    _case(torch.float32, B, n_new, D, Hkv, d, rng.integers(0, 9, B).tolist(), 16, pos, fire=fire, seed=50 + B)
