@@ -381,12 +381,11 @@ int verify_impl(const void *q, int B, int T, int Hq, int Hkv, int d, int dtype, 
         }
         return MAD_OK;
     }
-    mad::VerifyPlan p = mad::plan_verify(B, Hkv, G, T, len, vnat);
-    mad::VerifyArgs a;
+    mad::StreamArgs a;
     memset(&a, 0, sizeof(a));
     a.q = q;
     a.k = k;
-    a.vt = v;
+    a.v = v;
     a.vnat = vnat ? 1 : 0;
     a.out = out;
     a.lse = lse;
@@ -396,19 +395,14 @@ int verify_impl(const void *q, int B, int T, int Hq, int Hkv, int d, int dtype, 
     mad::verify_ws_layout(B, Hq, Hkv, d, T, &off_o, &off_ml);
     a.part = (float *)((char *)ws + off_o);
     a.part_ml = (float *)((char *)ws + off_ml);
+    a.counters = (unsigned *)ws;
     a.scale_log2 = scale * 1.4426950408889634f;
     a.cap = cap;
     a.Hq = Hq;
-    a.Hkv = Hkv;
     a.G = G;
     a.T = T;
-    a.d = d;
-    a.units = p.units;
-    a.n_splits = p.n_splits;
-    a.chunk = p.chunk;
-    a.part_rows = T * G;
-    for (int b = 0; b < B; ++b) a.len[b] = len[b];
-    return hip_status(mad::launch_verify(a, (hipStream_t)stream), "verify launch");
+    mad::plan_stream(a, B, Hkv, d, len);
+    return hip_status(mad::launch_stream(a, d, (hipStream_t)stream), "verify launch");
 }
 
 }  // namespace

@@ -174,6 +174,14 @@ __device__ __forceinline__ void store_agent2(float *p, float a, float b) {
     const uint64_t v = (uint64_t)__float_as_uint(a) | ((uint64_t)__float_as_uint(b) << 32);
     __hip_atomic_store(reinterpret_cast<uint64_t *>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// Four adjacent floats (16-byte aligned) in one device-scope store (no 16-byte
+// atomic exists).  The compiler does not count it: the caller's wait_vm_stores
+// does.  The s_nop keeps the next instruction off the data registers for the
+// one wait state a store of more than 8 bytes asks for.
+typedef float f32x4_agent __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store_agent4(float *p, f32x4_agent v) {
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" : : "v"(p), "v"(v) : "memory");
+}
 __device__ __forceinline__ uint64_t load_agent64(const uint64_t *p) {
     return __hip_atomic_load(const_cast<uint64_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -305,6 +313,26 @@ __device__ __forceinline__ void lds_stream16_nt(const void *src, void *lds_base)
     uint32_t saved;
     asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt\n\ts_mov_b32 m0, %0"
                  : "=&s"(saved) : "v"(src), "s"(m) : "memory");
+}
+// ... at device scope, for data written by other workgroups of the launch.
+__device__ __forceinline__ void lds_stream16_coherent(const void *src, void *lds_base) {
+    const uint32_t m = __builtin_amdgcn_readfirstlane(lds_addr(lds_base));
+    uint32_t saved;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off sc1\n\ts_mov_b32 m0, %0"
+                 : "=&s"(saved) : "v"(src), "s"(m) : "memory");
+}
+// Two streaming loads of a wave from a wave-uniform base with a 32-bit byte
+// offset per lane, to LDS address `lds` (wave-uniform) and the 1024 bytes after
+// it; the second load's instruction offset adds 1024 to its memory address too.
+__device__ __forceinline__ void lds_stream16_nt_x2(const void *base, uint32_t off0, uint32_t off1, uint32_t lds) {
+    const uint32_t m = __builtin_amdgcn_readfirstlane(lds);
+    uint64_t b = (uint64_t)(uintptr_t)base;
+    b = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)) << 32) |
+        (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b);
+    uint32_t saved;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3 nt\n\t"
+                 "global_load_lds_dwordx4 %2, %3 offset:1024 nt\n\ts_mov_b32 m0, %0"
+                 : "=&s"(saved) : "v"(off0), "v"(off1), "s"(b), "s"(m) : "memory");
 }
 // Load N dwords at a wave-uniform address through the scalar cache (s_load).
 template <int N>

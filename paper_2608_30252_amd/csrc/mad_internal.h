@@ -73,22 +73,42 @@ hipError_t launch_update(const UpdateArgs &a, int dtype, hipStream_t st);
 constexpr int kUpdateGemvRows = 8;   // bf16 updates of at most this many rows take the weight stream
 bool update_uses_gemv(int R, int D, int dtype);
 
-// ---------------------------------------------------------------- verify ----
-constexpr int kVerifyTargetWGs = 256;   // workgroups the split count aims at (one per CU)
-constexpr int kVerifyMaxSplits = 128;
+// ---------------------------------------------------------------- stream ----
+// bf16 attention over long key streams (stream.hip)
+constexpr int kStreamWGs = 256;   // workgroups of a launch: one per CU
+__host__ __device__ constexpr int stream_slab(int d) { return d == 128 ? 64 : 128; }   // keys per slab (32 KB of K + V)
 
-struct VerifyArgs {
-    const void *q, *k, *vt;   // vt: V in natural rows [cap][d] when vnat, else one run of cap keys per feature
+constexpr int kMergeBytes = 128 << 10;   // LDS a merging workgroup fills with pieces at a time
+
+struct StreamArgs {
+    const void *q, *k, *v;    // v: rows of d when vnat, else one run of cap keys per feature
     void *out;
     float *lse;
-    int64_t seq, head;    // element strides of sequences and KV heads (K and V^T alike)
-    float *part;          // [units][n_splits][part_rows][d] split partials (unnormalised o)
-    float *part_ml;       // [units][n_splits][part_rows][2] (max, sum)
+    int64_t seq, head;        // element strides of sequences and KV heads (K and V alike)
+    float *part, *part_ml;    // pieces: [T*G][d] unnormalised o, [T*G][2] (max in log2 units, sum)
+    unsigned *counters;       // counter region: unit u on line u
     float scale_log2;
-    int cap, Hq, Hkv, G, T, d, units, n_splits, chunk, part_rows;
-    int vnat;             // 1: V stored in natural rows
-    int len[kMaxB];
+    int cap, Hq, Hkv, G, T, vnat;
+    int n_wg, base, rem;      // workgroup w runs base (+ 1 for w < rem) consecutive slabs
+    int by_unit;              // 1: instead, the workgroups of a row's units split each unit evenly
+    int B, merge_nr;          // merge_nr > 0: the pieces are merged by a second launch, merge_nr rows a workgroup
+    int rows, wgs;            // slabs, and by_unit workgroups, of one KV head over all rows
+    // per row: keys, -, workgroups (by_unit) and slabs of the rows before it (one KV head); past the last row: the end
+    int4 row[kMaxB];
 };
+
+// the first slab of workgroup w's run, and the workgroup whose run holds slab x
+__host__ __device__ inline int stream_first(int w, int base, int rem) {
+    return w * base + (w < rem ? w : rem);
+}
+__host__ __device__ inline int stream_owner(int x, int base, int rem) {
+    const int big = rem * (base + 1);
+    return x < big ? x / (base + 1) : rem + (x - big) / base;
+}
+void plan_stream(StreamArgs &a, int B, int Hkv, int d, const int *n_keys);
+hipError_t launch_stream(const StreamArgs &a, int d, hipStream_t st);
+size_t verify_ws_bytes(int B, int Hq, int Hkv, int d, int T);
+void verify_ws_layout(int B, int Hq, int Hkv, int d, int T, size_t *off_o, size_t *off_ml);
 
 // ----------------------------------------------------------------- layer ----
 constexpr int kMaxLinRows = MAD_MAX_LAYER_ROWS;
@@ -121,15 +141,6 @@ struct PrefillArgs {
 
 int prefill_tokens_per_block(int d, int G);
 hipError_t launch_prefill(const PrefillArgs &a, int d, int G, hipStream_t st);
-
-struct VerifyPlan {
-    int units, n_splits, chunk;
-};
-
-VerifyPlan plan_verify(int B, int Hkv, int G, int T, const int *len, bool vnat);
-size_t verify_ws_bytes(int B, int Hq, int Hkv, int d, int T);
-void verify_ws_layout(int B, int Hq, int Hkv, int d, int T, size_t *off_o, size_t *off_ml);
-hipError_t launch_verify(const VerifyArgs &a, hipStream_t st);
 
 // ---------------------------------------------------------------- accept ----
 constexpr int kAcceptChunk = 8192;   // vocabulary entries per workgroup

@@ -1,0 +1,742 @@
+// stream.hip -- bandwidth-bound bf16 attention over long key/value streams: the
+// target's (gamma+1)-query verify attention over its full KV cache (Sec. 2.1
+// draft-verify paradigm; Sec. 3.3: the verifier keeps the full KV), query t of
+// the T = gamma+1 new tokens seeing rows 0 .. len-T+t.
+//
+// Work decomposition.  A unit is one (sequence, KV head); its query tile is the
+// T*G rows (t, g) -> row t*G + g, padded to 16-row blocks.  The keys of every
+// unit are cut into slabs (32 KB of K + V), and the slabs of all units, in unit
+// order, are dealt to one workgroup per CU in equal contiguous runs.  Ragged
+// batches therefore keep every CU busy to the end: with a fixed number of
+// splits per unit, sized by the longest sequence, 16 sequences of 600 .. 12000
+// keys ran at 3.5 TB/s.  A run covers whole units, the tail of its first unit
+// and the head of its last; whole units are finished by their workgroup,
+// pieces of a unit are merged by the last workgroup to arrive at it (one
+// arrival counter per unit), so a call is a single launch.
+//
+// Both products run on the matrix cores (v_mfma_f32_16x16x32_bf16, fp32
+// accumulation):
+//   * S^T = K Q^T takes K rows as the A operand.  Key rows are assigned to the
+//     A rows with a fixed permutation so that the S^T accumulator already holds,
+//     in every lane, the 8 consecutive keys that the next product needs;
+//   * O^T = V^T P^T takes its A operand (8 consecutive keys of one feature)
+//     either from V rows of d features (two transposing LDS reads,
+//     ds_read_b64_tr_b16) or from a key-contiguous V^T cache (one run of cap
+//     keys per feature); the probabilities come from the lane's own scores
+//     (rounded to bf16);
+//   * online softmax per query row: the row's 8 scores of a 32-key step sit in
+//     one lane, the row max needs two cross-lane exchanges.
+// The eight waves share a four-stage LDS ring of slabs filled by direct loads
+// (global_load_lds_dwordx4, issued by all waves), so 96 KB are in flight per
+// CU.  Wave w < KS*NB owns 16-row block w % NB and key group w / NB of every
+// slab; consecutive waves -- on different SIMDs -- take different row blocks,
+// and one wave's exponentials overlap another's matrix products.  K rows land
+// with their 16-byte chunks XOR-swizzled by row, V rows by 2 (row mod 4), V^T
+// rows by feature, so every operand read is conflict-free.  The ring runs on
+// across units: the next unit's slabs and its query rows (direct loads into a
+// small LDS area, older than the unit's first slab) are in flight while the
+// current unit finishes.
+#include "mad_device.h"
+#include "mad_internal.h"
+
+namespace mad {
+
+// phase marks of the diagnostic trace build: 0 entry, 1 the run's last slab done
+MAD_TRACE_BUFFER(mad_trace_verify)
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_v;
+typedef __attribute__((ext_vector_type(4))) float f32x4_v;
+typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_v;
+
+// Lanes l, l^16, l^32, l^48 hold the same query row: two lane swaps reduce over the four.
+__device__ __forceinline__ float max_over_row_lanes(float v) { return pair_max<32>(pair_max<16>(v)); }
+__device__ __forceinline__ float sum_over_row_lanes(float v) { return pair_sum<32>(pair_sum<16>(v)); }
+
+template <int D, int NB>
+struct StreamCfg {
+    static constexpr int SLAB = stream_slab(D);            // keys per slab
+    static constexpr int RB = D * 2;                       // bytes per K (and V) row
+    static constexpr int CPR = D / 8;                      // 16-byte chunks per row
+    static constexpr int KBYTES = SLAB * RB;               // K bytes per slab (= V bytes)
+    static constexpr int STAGE = 2 * KBYTES;
+    static constexpr int NST = 4;                          // ring stages
+    static constexpr int NWV = 8;                          // waves
+    static constexpr int IPW = STAGE / 1024 / NWV;         // direct loads per wave per slab
+    static constexpr int RP = NB * 16;                     // padded query rows
+    static constexpr int KS = SLAB / 32 < NWV / NB ? SLAB / 32 : (NWV / NB >= 4 ? 4 : 2);   // key groups of a slab
+    static constexpr int KPG = SLAB / KS;                  // keys per group: 32, or 64 in two steps
+    static constexpr int VROW = SLAB * 2, VCH = SLAB / 8;  // bytes and chunks of a V^T row in a stage
+    static constexpr int QBYTES = RP * RB;
+    static constexpr int QSLOTS = RP * RB >= 16384 ? 1 : 2;   // query areas (LDS holds one at 64 rows, d 128)
+    static constexpr int OFF_Q = NST * STAGE;
+    static constexpr int OFF_ML = OFF_Q + QSLOTS * QBYTES;
+    static constexpr int SMEM = OFF_ML + KS * RP * 8;
+    static constexpr int XPASS = KS * RP * D * 4 > STAGE ? 2 : 1;   // passes of the key groups' exchange through one stage
+    static_assert((NST * STAGE & (NST * STAGE - 1)) == 0 && IPW % 2 == 0 && KS * NB <= NWV && KPG % 32 == 0, "waves");
+    static_assert(KS * RP * D * 4 <= XPASS * STAGE, "the key groups' exchange fits one stage");
+    static_assert(SMEM + 64 <= 160 * 1024, "LDS");
+};
+
+__device__ __forceinline__ int vk_swz(int k) { return (k & 3) | (((k >> 3) & 1) << 2); }
+// natural V rows: 16-byte chunk c of key row k sits at chunk c ^ vn_swz(k); a
+// transposing read of 16 lanes covers rows k0 .. k0+3 (k0 a multiple of 4) x
+// two adjacent chunks, and XOR with 2 (k mod 4) puts the eight (row, chunk)
+// pairs on distinct banks
+__device__ __forceinline__ int vn_swz(int k) { return (k & 3) << 1; }
+typedef short v4s_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ v4s_t lds_read_tr16(const unsigned char *p) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s_t *)(p));
+}
+
+// The kernel arguments, read at entry in one batch (one wait) and kept: left to
+// the compiler they are read in dependent rounds where they are used, each a
+// miss to host memory once the key stream has swept the L2.  The row records
+// come in the same batch, one per lane, and are taken from there by readlane.
+struct StreamCtx {
+    uint64_t q, k, v, out, lse, part, part_ml, counters;
+    int64_t seq, head;
+    float cs;
+    int cap, Hq, Hkv, G, T, base, rem, by_unit, merge_nr, rows, wgs;   // rows, wgs: slabs and (by_unit) workgroups of one KV head over all rows
+    int4 rec;   // lane b: row b's record
+    __device__ __forceinline__ int tile0(int b) const { return __builtin_amdgcn_readlane(rec.w, b); }
+    __device__ __forceinline__ int slabs(int b) const { return (b == kMaxB - 1 ? rows : tile0(b + 1)) - tile0(b); }
+    __device__ __forceinline__ int wg0(int b) const { return __builtin_amdgcn_readlane(rec.z, b); }
+    __device__ __forceinline__ int splits(int b) const { return (b == kMaxB - 1 ? wgs : wg0(b + 1)) - wg0(b); }
+    __device__ __forceinline__ int len(int b) const { return __builtin_amdgcn_readlane(rec.x, b); }
+};
+__device__ __forceinline__ StreamCtx load_ctx(const StreamArgs &a) {
+    StreamCtx x;
+    x.rec = a.row[threadIdx.x & 63];
+    x.q = ptr_bits(a.q); x.k = ptr_bits(a.k); x.v = ptr_bits(a.v); x.out = ptr_bits(a.out); x.lse = ptr_bits(a.lse);
+    x.part = ptr_bits(a.part); x.part_ml = ptr_bits(a.part_ml); x.counters = ptr_bits(a.counters);
+    x.seq = a.seq; x.head = a.head;
+    x.cs = a.scale_log2;
+    x.cap = a.cap; x.Hq = a.Hq; x.Hkv = a.Hkv; x.G = a.G; x.T = a.T; x.base = a.base; x.rem = a.rem;
+    x.by_unit = a.by_unit; x.merge_nr = a.merge_nr; x.rows = a.rows; x.wgs = a.wgs;
+    asm volatile("" : "+s"(x.q), "+s"(x.k), "+s"(x.v), "+s"(x.out), "+s"(x.lse), "+s"(x.part), "+s"(x.part_ml),
+                 "+s"(x.counters), "+s"(x.seq), "+s"(x.head), "+s"(x.cs));
+    asm volatile("" : "+s"(x.cap), "+s"(x.Hq), "+s"(x.Hkv), "+s"(x.G), "+s"(x.T), "+s"(x.base), "+s"(x.rem),
+                 "+s"(x.by_unit), "+s"(x.merge_nr), "+s"(x.rows), "+s"(x.wgs));
+    return x;
+}
+
+// where unit u's pieces are: np of them, the first numbered p0
+struct UnitPieces {
+    int p0, np;
+};
+__device__ __forceinline__ UnitPieces unit_pieces(const StreamCtx &a, int u) {
+    const int b = u / a.Hkv, c = u - b * a.Hkv;
+    if (a.by_unit) {
+        const int k = a.splits(b);
+        return {a.Hkv * a.wg0(b) + c * k + u, k};
+    }
+    const int nt = a.slabs(b), s0 = a.Hkv * a.tile0(b) + c * nt, w0 = stream_owner(s0, a.base, a.rem);
+    return {w0 + u, stream_owner(s0 + nt - 1, a.base, a.rem) - w0 + 1};
+}
+
+// Log-sum-exp merge of rows [ra, ra + nr) of unit u from its pieces, by a
+// workgroup of 512 threads, in three steps with a barrier after each: the
+// pieces into LDS in one round trip of device-coherent direct loads (o at
+// `so`, 16 bytes aligned, np * nr * D * 4 of them), their (max, sum) beside it;
+// eight lanes per row turn those into weights while the rest arrives; the sums.
+// np * nr <= 512.
+template <int D>
+struct MergeJob {
+    int u, p0, np, ra, nr;
+    unsigned char *so;
+    float2 *sml;    // [np][nr]
+    float *sinv;    // [nr]
+
+    // the (max, sum) pairs, one a thread
+    __device__ __forceinline__ uint64_t load_ml(const StreamCtx &a) const {
+        const int pp = threadIdx.x / nr;
+        return pp < np ? load_agent64(bits_ptr<const uint64_t>(a.part_ml) + (size_t)(p0 + pp) * (a.T * a.G) + ra + ((int)threadIdx.x - pp * nr)) : 0;
+    }
+    __device__ __forceinline__ void load_o(const StreamCtx &a) const {
+        // 16-byte chunk x of [np][q]: x and its (piece, offset) advance by 512 a step; the last step's surplus lanes read the last chunk
+        const int tid = threadIdx.x, R = a.T * a.G, q = nr * (D / 4), total = np * q, dp = 512 / q, dx = 512 - dp * q;
+        const float *po = bits_ptr<const float>(a.part) + (size_t)p0 * R * D;
+        int pc = tid / q, off = tid - pc * q;
+        for (int x0 = tid & ~63; x0 < total; x0 += 512) {
+            const bool in = pc < np;
+            lds_stream16_coherent(po + ((size_t)(in ? pc : np - 1) * R + ra) * D + (in ? off : q - 1) * 4, so + x0 * 16);
+            pc += dp;
+            off += dx;
+            if (off >= q) {
+                off -= q;
+                ++pc;
+            }
+        }
+    }
+    __device__ __forceinline__ void store_ml(uint64_t v) const {
+        if ((int)threadIdx.x < np * nr) sml[threadIdx.x] = make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
+    }
+    __device__ __forceinline__ size_t head(const StreamCtx &a, int r) const {
+        const int b = u / a.Hkv, c = u - b * a.Hkv, row = ra + r, tt = row / a.G;
+        return ((size_t)b * a.T + tt) * a.Hq + (size_t)c * a.G + (row - tt * a.G);
+    }
+    __device__ __forceinline__ void weights(const StreamCtx &a) const {
+        for (int r = threadIdx.x >> 3; r < nr; r += 64) {
+            const int l8 = threadIdx.x & 7;
+            float M = -INFINITY, L = 0.f;
+            for (int p = l8; p < np; p += 8) M = fmaxf(M, sml[p * nr + r].x);
+            M = group_max<8>(M);
+            const float mr = M == -INFINITY ? 0.f : M;
+            for (int p = l8; p < np; p += 8) {
+                const float2 v = sml[p * nr + r];
+                const float wt = __builtin_amdgcn_exp2f(v.x - mr);
+                L = fmaf(wt, v.y, L);
+                sml[p * nr + r].x = wt;
+            }
+            L = group_sum<8>(L);
+            if (l8 == 0) {
+                sinv[r] = L > 0.f ? 1.f / L : 0.f;
+                if (a.lse) bits_ptr<float>(a.lse)[head(a, r)] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
+            }
+        }
+    }
+    __device__ __forceinline__ void sums(const StreamCtx &a) const {
+        const int q = nr * (D / 4);
+        for (int x = threadIdx.x; x < q; x += 512) {   // feature quad x % (D / 4) of row x / (D / 4)
+            const int r = x / (D / 4);
+            f32x4_v y = f32x4_v{0.f, 0.f, 0.f, 0.f};
+            #pragma unroll 8
+            for (int p = 0; p < np; ++p) {
+                const f32x4_v v = *reinterpret_cast<const f32x4_v *>(so + (size_t)(p * q + x) * 16);
+                const float wt = sml[p * nr + r].x;
+                #pragma unroll
+                for (int e = 0; e < 4; ++e) y[e] = fmaf(wt, v[e], y[e]);
+            }
+            const float inv = sinv[r];
+            *reinterpret_cast<uint2 *>(bits_ptr<bf16_t>(a.out) + head(a, r) * D + (x % (D / 4)) * 4) =
+                make_uint2(pack_bf16x2(y[0] * inv, y[1] * inv), pack_bf16x2(y[2] * inv, y[3] * inv));
+        }
+    }
+};
+
+// rows [r0, r1) of unit u, as many at a time as fit kMergeBytes of LDS
+template <int D>
+__device__ __forceinline__ void merge_rows(const StreamCtx &a, int u, UnitPieces up, int r0, int r1, unsigned char *smem,
+                                           float2 *sml) {
+    __shared__ float sinv[MAD_MAX_VERIFY_ROWS];
+    const int most = kMergeBytes / (up.np * D * 4);   // at least 1: np <= kStreamWGs
+    for (int ra = r0; ra < r1; ra += most) {
+        const MergeJob<D> j = {u, up.p0, up.np, ra, min(most, r1 - ra), smem, sml, sinv};
+        const uint64_t ml = j.load_ml(a);
+        __syncthreads();   // earlier readers of smem and sml are done
+        j.load_o(a);
+        j.store_ml(ml);
+        __syncthreads();
+        j.weights(a);
+        wait_vm(0);
+        __syncthreads();
+        j.sums(a);
+    }
+}
+
+template <int D, int NB, bool VNAT>
+__global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
+    using C = StreamCfg<D, NB>;
+    constexpr int KST = D / 32, DB = D / 16;
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ int s_last[2];
+    MAD_TRACE_T0();
+    const StreamCtx a = load_ctx(args);
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lr = lane & 15, lg = lane >> 4;
+    const int w = blockIdx.x;
+    const int T = a.T, G = a.G, R = T * G, Hkv = a.Hkv;
+
+    // ---- this workgroup's run of slabs: the first one's unit (b, c) and slab t, and their number ----
+    int b, c, t, left;
+    if (a.by_unit) {
+        b = __popcll(__ballot(Hkv * a.rec.z <= w)) - 1;   // records past the last row hold the end
+        const int k = a.splits(b), rel = w - Hkv * a.wg0(b), n0 = a.slabs(b);
+        c = rel / k;
+        const int part = rel - c * k, lo = n0 / k, hi = n0 - lo * k;   // hi pieces of lo + 1 slabs, then of lo
+        t = part * lo + min(part, hi);
+        left = lo + (part < hi ? 1 : 0);
+    } else {
+        const int g0 = stream_first(w, a.base, a.rem);
+        left = stream_first(w + 1, a.base, a.rem) - g0;
+        b = __popcll(__ballot(Hkv * a.rec.w <= g0)) - 1;
+        const int n0 = a.slabs(b), rel = g0 - Hkv * a.tile0(b);
+        c = rel / n0;
+        t = rel - c * n0;
+    }
+
+    // ---- issue side: the next slab to load is slab i_t of unit (i_b, i_c) ----
+    const int wv = __builtin_amdgcn_readfirstlane(wave);
+    int i_b = b, i_c = c, i_t = t, i_left = left, i_nt = 0;
+    int issued = 0, q_issued = 0, q_done = 0;   // slabs; query areas filled, and copied to registers
+    int i_stage = 0;                            // stage of the slab, bytes
+    int64_t i_keys = 0;                         // the unit's keys from the slab on
+    const bf16_t *i_k = nullptr, *i_v = nullptr;   // the slab's K and V rows (V^T: the unit's first feature)
+    auto i_unit = [&]() {
+        i_nt = a.slabs(i_b);
+        i_keys = a.len(i_b) - (int64_t)i_t * C::SLAB;
+        i_k = bits_ptr<const bf16_t>(a.k) + i_b * a.seq + i_c * a.head + (int64_t)i_t * C::SLAB * D;
+        i_v = bits_ptr<const bf16_t>(a.v) + i_b * a.seq + i_c * a.head + (VNAT ? (int64_t)i_t * C::SLAB * D : 0);
+    };
+    i_unit();
+    // K and natural V: lane l of wave load inst fetches row cidx / CPR (cidx = 64 inst + l) of the
+    // slab; LDS slot cidx % CPR of the row holds its chunk slot ^ swizzle(row).  A wave's load j adds
+    // 1024 j to both of its addresses (an instruction offset), so its lane offset leaves that out.
+    constexpr int LPW = C::IPW / 2;   // K (and V) loads per wave
+    uint32_t k_off[LPW], v_off[LPW];
+    #pragma unroll
+    for (int j = 0; j < LPW; ++j) {
+        const int cidx = (wave * LPW + j) * 64 + lane, kr = cidx / C::CPR, slot = cidx % C::CPR;
+        k_off[j] = kr * C::RB + ((slot ^ vk_swz(kr)) << 4) - 1024 * j;
+        v_off[j] = kr * C::RB + ((slot ^ vn_swz(kr)) << 4) - 1024 * j;
+    }
+    static_assert(LPW == 2, "lds_stream16_nt_x2");
+    const uint32_t ring = __builtin_amdgcn_readfirstlane(lds_addr(smem)) + wv * LPW * 1024;
+    // the first slab of a unit (or of the run) needs a free query area
+    auto can_issue = [&]() {
+        return i_left > 0 && ((i_t > 0 && issued > 0) || q_issued - q_done < C::QSLOTS);
+    };
+    auto issue = [&]() {
+        if (i_t == 0 || issued == 0) {
+            // the unit's query rows, 1 KB per wave load; lanes past them fetch the last chunk again
+            unsigned char *qa = smem + C::OFF_Q + (C::QSLOTS == 2 ? (q_issued & 1) * C::QBYTES : 0);
+            const bf16_t *qb = bits_ptr<const bf16_t>(a.q) + ((size_t)i_b * T * a.Hq + (size_t)i_c * G) * D;
+            for (int p = wv; p * 1024 < R * C::RB; p += C::NWV) {
+                const int ch = min(p * 64 + lane, R * C::CPR - 1), r = ch / C::CPR, tt = r / G;
+                lds_stream16(qb + ((size_t)tt * a.Hq + (r - tt * G)) * D + (ch % C::CPR) * 8, qa + p * 1024);
+            }
+            ++q_issued;
+        }
+        if (VNAT && i_keys >= C::SLAB) {   // every row of the slab exists: one base and fixed lane offsets
+            lds_stream16_nt_x2(i_k, k_off[0], k_off[1], ring + i_stage);
+            lds_stream16_nt_x2(i_v, v_off[0], v_off[1], ring + i_stage + C::KBYTES);
+        } else {
+            unsigned char *st = smem + i_stage;
+            const int keys = (int)min(i_keys, (int64_t)C::SLAB);
+            #pragma unroll
+            for (int j = 0; j < LPW; ++j) {
+                const int inst = wv * LPW + j;
+                const int cidx = inst * 64 + lane;
+                const int kr = cidx / C::CPR, slot = cidx % C::CPR;
+                const int key = min(kr, keys - 1);   // rows past len: a valid row, masked
+                lds_stream16_nt(i_k + key * D + (slot ^ vk_swz(kr)) * 8, st + inst * 1024);
+                if constexpr (VNAT) {
+                    lds_stream16_nt(i_v + key * D + (slot ^ vn_swz(kr)) * 8, st + C::KBYTES + inst * 1024);
+                } else {
+                    // V^T: feature cidx / VCH, LDS slot holds key chunk slot ^ (f & 7)
+                    const int f = cidx / C::VCH, vs = cidx % C::VCH;
+                    int kc = i_t * C::SLAB + ((vs ^ (f & 7)) << 3);
+                    if (kc + 8 > a.cap) kc = a.cap - 8;      // chunks past the cache: any valid chunk (zeroed when used)
+                    lds_stream16_nt(i_v + (size_t)f * a.cap + kc, st + C::KBYTES + inst * 1024);
+                }
+            }
+        }
+        ++issued;
+        --i_left;
+        i_stage = (i_stage + C::STAGE) & (C::NST * C::STAGE - 1);
+        i_keys -= C::SLAB;
+        i_k += C::SLAB * D;
+        if (VNAT) i_v += C::SLAB * D;
+        if (++i_t == i_nt && i_left > 0) {
+            i_t = 0;
+            if (++i_c == Hkv) {
+                i_c = 0;
+                ++i_b;
+            }
+            i_unit();
+        }
+    };
+
+    // ---- compute side: row block rbw, key group kg of every slab ----
+    const int rbw = wave % NB, kg = wave / NB, row = rbw * 16 + lr;
+    const bool active = kg < C::KS;
+    const int row_t = min(row, R - 1) / G;   // this row's query index t
+    bf16x8_v qf[KST];
+    int len = 0, lim = 0, nt = 0;
+    f32x4_v o[DB];
+    float m_run = -INFINITY, l_run = 0.f;
+    const float cs = a.cs;
+
+    auto start_unit = [&]() {
+        nt = a.slabs(b);
+        len = a.len(b);
+        lim = len - T + row_t;
+        const unsigned char *qa = smem + C::OFF_Q + (C::QSLOTS == 2 ? (q_done & 1) * C::QBYTES : 0) + min(row, R - 1) * C::RB;
+        #pragma unroll
+        for (int ks = 0; ks < KST; ++ks) qf[ks] = *reinterpret_cast<const bf16x8_v *>(qa + ks * 64 + lg * 16);
+        m_run = -INFINITY;
+        l_run = 0.f;
+        #pragma unroll
+        for (int db = 0; db < DB; ++db) o[db] = f32x4_v{0.f, 0.f, 0.f, 0.f};
+    };
+
+    // 32 keys of the slab, from key 32 kh of it
+    auto compute = [&](const unsigned char *st, int kb, int kh) {
+        // A row m of block blk is key 32 kh + 8(m/4) + 4 blk + m%4 of the slab, so
+        // accumulator element e&3 of block e>>2 is key 32 kh + 8 lg + e
+        // Every operand of the step is read at once, so V's LDS latency runs behind the scores and the softmax.
+        bf16x8_v kf[2][KST], vf[DB];
+        #pragma unroll
+        for (int blk = 0; blk < 2; ++blk) {
+            const int kr = 32 * kh + 8 * (lr >> 2) + 4 * blk + (lr & 3);
+            #pragma unroll
+            for (int ks = 0; ks < KST; ++ks)
+                kf[blk][ks] = *reinterpret_cast<const bf16x8_v *>(st + kr * C::RB + (((4 * ks + lg) ^ vk_swz(kr)) << 4));
+        }
+        const unsigned char *sv8 = st + C::KBYTES;
+        if constexpr (VNAT) {
+            // A = V^T rows (features db*16 + lr), keys 32 kh + 8 lg .. +7, from
+            // the transposing reads of key rows 32 kh + 8 lg + {0..3} and {4..7}
+            // (rows past len hold the clamped row len - 1, weighted 0)
+            const int r0 = 32 * kh + 8 * lg + (lr >> 2), r1 = r0 + 4, tr_byte = 8 * (lr & 3);
+            #pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                const int byte = db * 32 + tr_byte, chunk = byte >> 4, half = byte & 8;
+                const v4s_t lo = lds_read_tr16(sv8 + r0 * C::RB + ((chunk ^ vn_swz(r0)) << 4) + half);
+                const v4s_t hi = lds_read_tr16(sv8 + r1 * C::RB + ((chunk ^ vn_swz(r1)) << 4) + half);
+                vf[db] = __builtin_bit_cast(bf16x8_v, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            }
+        } else {
+            #pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                const int f = db * 16 + lr;
+                vf[db] = *reinterpret_cast<const bf16x8_v *>(sv8 + f * C::VROW + (((4 * kh + lg) ^ (f & 7)) << 4));
+            }
+        }
+        f32x4_v sacc[2];
+        #pragma unroll
+        for (int blk = 0; blk < 2; ++blk) {
+            sacc[blk] = f32x4_v{0.f, 0.f, 0.f, 0.f};
+            #pragma unroll
+            for (int ks = 0; ks < KST; ++ks)
+                sacc[blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[blk][ks], qf[ks], sacc[blk], 0, 0, 0);
+        }
+        float sv[8];
+        float mt = -INFINITY;
+        const int kg0 = kb + 32 * kh + 8 * lg;
+        if (__all(kb + C::SLAB - 1 <= lim)) {
+            #pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                sv[j] = sacc[j >> 2][j & 3];
+                mt = fmaxf(mt, sv[j]);
+            }
+        } else {
+            #pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                sv[j] = kg0 + j <= lim ? sacc[j >> 2][j & 3] : -INFINITY;
+                mt = fmaxf(mt, sv[j]);
+            }
+        }
+        mt = max_over_row_lanes(mt);
+        const float mn = fmaxf(m_run, mt);
+        const bool same = mn == m_run;
+        const float ms = (mn == -INFINITY) ? 0.f : mn * cs;
+        const float alpha = same ? 1.f : __builtin_amdgcn_exp2f(fmaf(m_run, cs, -ms));
+        m_run = mn;
+        float ps = 0.f;
+        uint32_t pk[4];
+        #pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float p0 = __builtin_amdgcn_exp2f(fmaf(sv[2 * e], cs, -ms));
+            const float p1 = __builtin_amdgcn_exp2f(fmaf(sv[2 * e + 1], cs, -ms));
+            ps += p0 + p1;
+            pk[e] = cvt_pk_bf16(p0, p1);
+        }
+        const bf16x8_v pf = __builtin_bit_cast(bf16x8_v, u32x4_v{pk[0], pk[1], pk[2], pk[3]});
+        l_run = fmaf(l_run, alpha, ps);
+        if (!__all(same)) {
+            #pragma unroll
+            for (int db = 0; db < DB; ++db) o[db] *= alpha;
+        }
+        #pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            if constexpr (!VNAT) {
+                if (kg0 + 8 > len) {   // values of keys past len may be anything: zero them
+                    u32x4_v x = __builtin_bit_cast(u32x4_v, vf[db]);
+                    #pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int kk = kg0 + 2 * e;
+                        if (kk >= len) x[e] = 0u;
+                        else if (kk + 1 >= len) x[e] &= 0x0000ffffu;
+                    }
+                    vf[db] = __builtin_bit_cast(bf16x8_v, x);
+                }
+            }
+            o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[db], pf, o[db], 0, 0, 0);
+        }
+    };
+
+    // ---- end of a unit's run in this workgroup: the key groups' results go to
+    // the stage just read (the next load into it is issued behind the loop's
+    // next barrier), chunks swizzled by row, and every thread merges whole
+    // 16-byte chunks: either the unit's result or its piece for the merge.
+    // Written straight from the accumulators (16 rows, 32 bytes of each, a
+    // wave store) with unswizzled exchange rows a flush stalled the stream for
+    // 2.6 us at 48 rows, d 128; so 1.6 us. ----
+    int pu0 = -1, pu1 = -1;   // units of which this run holds a piece: begun by an earlier workgroup, begun here
+    float *lse = bits_ptr<float>(a.lse);
+    auto flush = [&](unsigned char *st, bool from0) {
+        const bool whole = from0 && t == nt;   // every slab of the unit ran here
+        const int u = b * Hkv + c;
+        if (!from0) pu0 = u;
+        else if (!whole) pu1 = u;
+        constexpr int DP = D / C::XPASS, QP = DP / 4;                 // features, chunks of a row per pass
+        float2 *xml = reinterpret_cast<float2 *>(smem + C::OFF_ML);   // [KS][RP]
+        const float lt = sum_over_row_lanes(l_run);
+        #pragma unroll
+        for (int ps = 0; ps < C::XPASS; ++ps) {
+            __syncthreads();   // every wave is done with the stage
+            if (active) {
+                #pragma unroll
+                for (int db = 0; db < DP / 16; ++db)
+                    *reinterpret_cast<f32x4_v *>(st + ((kg * C::RP + row) * QP + ((db * 4 + lg) ^ (row & (QP - 1) & 15))) * 16) =
+                        o[ps * (DP / 16) + db];
+                if (ps == 0 && lg == 0) xml[kg * C::RP + row] = make_float2(m_run == -INFINITY ? -INFINITY : m_run * cs, lt);
+            }
+            __syncthreads();
+            for (int x = tid; x < R * QP; x += 512) {
+                const int r = x / QP, ch = x % QP;
+                float m[C::KS], M = -INFINITY, L = 0.f;
+                f32x4_v y = f32x4_v{0.f, 0.f, 0.f, 0.f};
+                #pragma unroll
+                for (int k = 0; k < C::KS; ++k) {
+                    m[k] = xml[k * C::RP + r].x;
+                    M = fmaxf(M, m[k]);
+                }
+                #pragma unroll
+                for (int k = 0; k < C::KS; ++k) {
+                    const float wt = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[k] - M);
+                    const f32x4_v v = *reinterpret_cast<const f32x4_v *>(st + ((k * C::RP + r) * QP + (ch ^ (r & (QP - 1) & 15))) * 16);
+                    L = fmaf(wt, xml[k * C::RP + r].y, L);
+                    #pragma unroll
+                    for (int e = 0; e < 4; ++e) y[e] = fmaf(wt, v[e], y[e]);
+                }
+                if (whole) {
+                    const int tt = r / G;
+                    const size_t head = ((size_t)b * T + tt) * a.Hq + (size_t)c * G + (r - tt * G);
+                    const float inv = L > 0.f ? 1.f / L : 0.f;
+                    *reinterpret_cast<uint2 *>(bits_ptr<bf16_t>(a.out) + head * D + ps * DP + ch * 4) =
+                        make_uint2(pack_bf16x2(y[0] * inv, y[1] * inv), pack_bf16x2(y[2] * inv, y[3] * inv));
+                    if (lse && ps == 0 && ch == 0) lse[head] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
+                } else {
+                    // workgroups and units both advance in slab order, so w + u numbers the pieces one after the other
+                    const size_t pr = (size_t)(w + u) * R + r;
+                    store_agent4(bits_ptr<float>(a.part) + pr * D + ps * DP + ch * 4, y);
+                    if (ps == 0 && ch == 0) store_agent2(bits_ptr<float>(a.part_ml) + pr * 2, M, L);
+                }
+            }
+        }
+    };
+
+    while (issued < C::NST - 1 && can_issue()) issue();
+    bool first = true;   // the run's first unit
+    int c_stage = 0;
+    for (int i = 0; i < left; ++i) {
+        if (issued <= i) {   // the slab waited for a query area, which every wave has read by now
+            __syncthreads();
+            issue();
+        }
+        wait_vm(C::IPW * (issued - 1 - i));   // slab i has landed (this wave's part; newer query loads only make it stricter)
+        __syncthreads();                      // ... every wave's part; stage (i-1) % NST is free
+        while (issued < i + C::NST && can_issue()) issue();
+        if (t == 0 || i == 0) {
+            start_unit();
+            ++q_done;
+        }
+        unsigned char *st = smem + c_stage;
+        c_stage = (c_stage + C::STAGE) & (C::NST * C::STAGE - 1);
+        if (active) {
+            #pragma unroll
+            for (int h = 0; h < C::KPG / 32; ++h) compute(st, t * C::SLAB, kg * (C::KPG / 32) + h);
+        }
+        ++t;
+        if (t == nt || i == left - 1) {
+            flush(st, !first || i + 1 == t);
+            first = false;
+            if (t == nt) {
+                t = 0;
+                if (++c == Hkv) {
+                    c = 0;
+                    ++b;
+                }
+            }
+        }
+    }
+    MAD_TRACE_SAVE_T0(mad_trace_verify);
+    MAD_TRACE(mad_trace_verify, 1);
+    if ((pu0 < 0 && pu1 < 0) || a.merge_nr > 0) return;
+
+    // ---- arrivals; the last workgroup at a unit merges its pieces ----
+    wait_vm_stores();
+    __syncthreads();
+    MAD_TRACE(mad_trace_verify, 2);
+    const UnitPieces up0 = unit_pieces(a, max(pu0, 0)), up1 = unit_pieces(a, max(pu1, 0));
+    if (tid == 0 || tid == 64) {
+        const int u = tid == 0 ? pu0 : pu1;
+        int last = 0;
+        if (u >= 0) {
+            unsigned *cnt = bits_ptr<unsigned>(a.counters) + (size_t)u * kCounterStride;
+            last = arrive(cnt) == (unsigned)((tid == 0 ? up0.np : up1.np) - 1);
+            if (last) reset_counter(cnt);
+        }
+        s_last[tid >> 6] = last;
+    }
+    __syncthreads();
+    MAD_TRACE(mad_trace_verify, 3);
+    float2 *sml = reinterpret_cast<float2 *>(smem + C::OFF_Q);
+    if (s_last[0] && s_last[1] && (up0.np + up1.np) * R * D * 4 <= kMergeBytes) {
+        // last at both of its units: both merges behind one round trip
+        __shared__ float sinv[2 * MAD_MAX_VERIFY_ROWS];
+        const MergeJob<D> j0 = {pu0, up0.p0, up0.np, 0, R, smem, sml, sinv};
+        const MergeJob<D> j1 = {pu1, up1.p0, up1.np, 0, R, smem + up0.np * R * D * 4, sml + up0.np * R, sinv + R};
+        const uint64_t ml0 = j0.load_ml(a), ml1 = j1.load_ml(a);
+        j0.load_o(a);
+        j1.load_o(a);
+        j0.store_ml(ml0);
+        j1.store_ml(ml1);
+        __syncthreads();
+        j0.weights(a);
+        j1.weights(a);
+        wait_vm(0);
+        __syncthreads();
+        j0.sums(a);
+        j1.sums(a);
+    } else {
+        if (s_last[0]) merge_rows<D>(a, pu0, up0, 0, R, smem, sml);
+        if (s_last[1]) merge_rows<D>(a, pu1, up1, 0, R, smem, sml);
+    }
+    MAD_TRACE(mad_trace_verify, 4);
+}
+
+// The merge as a launch of its own, one workgroup per unit and merge_nr rows
+// (a workgroup past the unit's rows, or at a unit in one piece, has nothing to do).
+template <int D>
+__global__ __launch_bounds__(512, 1) void stream_merge_kernel(const StreamArgs args) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const StreamCtx a = load_ctx(args);
+    const int u = blockIdx.x, r0 = blockIdx.y * a.merge_nr;
+    const int R = a.T * a.G;
+    const UnitPieces p = unit_pieces(a, u);
+    if (p.np == 1 || r0 >= R) return;
+    merge_rows<D>(a, u, p, r0, min(R, r0 + a.merge_nr), smem, reinterpret_cast<float2 *>(smem + kMergeBytes));
+}
+
+// ------------------------------------------------------------------ host ----
+
+// One workgroup per CU (its ring fills most of the LDS); fewer when there are
+// fewer slabs.  Two ways to deal the slabs, by the longest share they give:
+//   by unit   unit (b, c) is cut into k_b even pieces, k_b as the row's length
+//             asks: no workgroup crosses a unit, every unit has few pieces;
+//   runs      equal contiguous runs over all units in unit order, for ragged
+//             batches whose pieces would come out uneven.
+// A run that crosses into the next unit stalls once (the flush, 1.6 us at 48
+// rows, d 128) and units get one piece more, so by unit is taken up to 1/16
+// above the even share: 4 sequences of 32773 keys (513 slabs a unit) took
+// 88.7 us in runs, 87.1 by unit; 16 of 600 .. 12000 keys 74 us in runs (100 with
+// splits of one length).  By unit also serves launches with more units than workgroups can
+// count (a unit each: no pieces, no counters).
+void plan_stream(StreamArgs &a, int B, int Hkv, int d, const int *n_keys) {
+    const int slab = stream_slab(d);
+    int64_t rows = 0;
+    int nt[kMaxB], nt_max = 1;
+    for (int b = 0; b < B; ++b) {
+        nt[b] = n_keys[b] > 0 ? (n_keys[b] - 1) / slab + 1 : 1;
+        a.row[b].x = n_keys[b];
+        a.row[b].w = (int)rows;
+        rows += nt[b];
+        nt_max = nt[b] > nt_max ? nt[b] : nt_max;
+    }
+    for (int b = B; b < kMaxB; ++b) a.row[b].w = (int)rows;
+    a.rows = (int)rows;
+    const int64_t total = rows * Hkv;
+    a.B = B;
+    a.Hkv = Hkv;
+    a.merge_nr = 0;
+    const bool whole = (int64_t)B * Hkv > kCounterLines || total > 0x3fffffff;   // a unit each
+    a.n_wg = total < kStreamWGs ? (int)total : kStreamWGs;
+    a.base = whole ? 1 : (int)(total / a.n_wg);
+    a.rem = whole ? 0 : (int)(total % a.n_wg);
+    int np_max = 1;
+    const int even = a.base + (a.rem > 0 ? 1 : 0);
+    a.by_unit = 0;
+    for (int share = whole ? nt_max : even; whole || share <= even + even / 16; share += 1 + even / 64) {
+        int wgs = 0;
+        np_max = 1;
+        for (int b = 0; b < B; ++b) {
+            const int k = (nt[b] - 1) / share + 1;
+            a.row[b].z = wgs;
+            wgs += k;
+            np_max = k > np_max ? k : np_max;
+        }
+        if (!whole && wgs * Hkv > kStreamWGs) continue;
+        for (int b = B; b < kMaxB; ++b) a.row[b].z = wgs;
+        a.by_unit = 1;
+        a.wgs = wgs;
+        a.n_wg = wgs * Hkv;
+        break;
+    }
+    if (!a.by_unit) {
+        np_max = (nt_max - 1) / a.base + 2;
+        np_max = np_max > a.n_wg ? a.n_wg : np_max;
+    }
+    // a unit in np pieces merges np T G d floats.  Up to two LDS fulls the last workgroup there does it
+    // in the launch (4 us at 10 pieces of 20 rows, d 128); more are spread over a second launch (5.8 us at
+    // 33 pieces of 40 rows, six LDS fulls)
+    const int64_t bytes = (int64_t)np_max * a.T * a.G * d * 4;
+    a.merge_nr = bytes > 2 * kMergeBytes ? kMergeBytes / (np_max * d * 4) / 4 + 1 : 0;
+}
+
+// pieces: at most one per workgroup and unit boundary
+size_t verify_ws_bytes(int B, int Hq, int Hkv, int d, int T) {
+    size_t off_o, off_ml;
+    verify_ws_layout(B, Hq, Hkv, d, T, &off_o, &off_ml);
+    const size_t pieces = (size_t)B * Hkv + kStreamWGs, rows = (size_t)T * (Hq / Hkv);
+    const size_t bf = off_ml + align256(pieces * rows * 2 * 4);
+    // fp32 verify runs the decode kernel once per sequence, its T query rows as the rows
+    const size_t f32 = decode_ws_bytes(T, Hq, Hkv, d);
+    return bf > f32 ? bf : f32;
+}
+
+void verify_ws_layout(int B, int Hq, int Hkv, int d, int T, size_t *off_o, size_t *off_ml) {
+    const size_t pieces = (size_t)B * Hkv + kStreamWGs, rows = (size_t)T * (Hq / Hkv);
+    *off_o = kCounterRegionBytes;
+    *off_ml = kCounterRegionBytes + align256(pieces * rows * d * 4);
+}
+
+template <int D, int NB>
+static hipError_t launch_nb(const StreamArgs &a, hipStream_t st) {
+    const dim3 grid((unsigned)a.n_wg), block(64 * StreamCfg<D, NB>::NWV);
+    if (a.vnat)
+        hipLaunchKernelGGL((stream_kernel<D, NB, true>), grid, block, (StreamCfg<D, NB>::SMEM), st, a);
+    else
+        hipLaunchKernelGGL((stream_kernel<D, NB, false>), grid, block, (StreamCfg<D, NB>::SMEM), st, a);
+    return hipGetLastError();
+}
+
+template <int D>
+static hipError_t launch_d(const StreamArgs &a, hipStream_t st) {
+    switch ((a.T * a.G + 15) / 16) {
+        case 1: return launch_nb<D, 1>(a, st);
+        case 2: return launch_nb<D, 2>(a, st);
+        case 3: return launch_nb<D, 3>(a, st);
+        case 4: return launch_nb<D, 4>(a, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+template <int D>
+static hipError_t launch_merge(const StreamArgs &a, hipStream_t st) {
+    const int chunks = (a.T * a.G + a.merge_nr - 1) / a.merge_nr;
+    hipLaunchKernelGGL((stream_merge_kernel<D>), dim3((unsigned)(a.B * a.Hkv), (unsigned)chunks), dim3(512), kMergeBytes + 4096, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_stream(const StreamArgs &a, int d, hipStream_t st) {
+    if (d != 64 && d != 128) return hipErrorInvalidValue;
+    const hipError_t e = d == 64 ? launch_d<64>(a, st) : launch_d<128>(a, st);
+    if (e != hipSuccess || a.merge_nr == 0) return e;
+    return d == 64 ? launch_merge<64>(a, st) : launch_merge<128>(a, st);
+}
+
+}  // namespace mad

@@ -21,7 +21,7 @@ key/value reads come from HBM):
   update_64       memory update of 64 rows (16 sequences x 4 slots), D 2048,
                   8 KV heads x d 64 (update_rows_kernel)
   verify_70b      verify attention, B1, 64/8 heads, d 128, 32768 + 5 keys, T 5
-                  (split kernel; the merge is a separate launch)
+                  (stream_kernel; its merge is a second launch at this size)
 """
 import argparse
 import ctypes
@@ -120,7 +120,7 @@ def report_verify(name, runs):
             dur.append(np.mean(r[:, 1] - r[:, 0]) * TICK_US)
     a = np.mean(ends, axis=0)
     print(f"{name}: {len(runs[0])} workgroups, {len(runs)} launches")
-    print(f"  workgroup starts spread over {np.mean(st):.2f} us; partials written {a[0]:.2f} / {a[1]:.2f} / "
+    print(f"  workgroup starts spread over {np.mean(st):.2f} us; last slab done {a[0]:.2f} / {a[1]:.2f} / "
           f"{a[2]:.2f} us (min / median / max); mean workgroup {np.mean(dur):.2f} us")
 
 

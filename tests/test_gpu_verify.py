@@ -185,3 +185,22 @@ def test_peaky_queries_full_size(B, Hq, c):
     targets = _make_peaky(q, k, length, c)
     out, lse = _run(q, k, v, length)
     _check(q, k, v, length, out, lse, targets)
+
+
+@pytest.mark.parametrize("layout", LAYOUTS)
+@pytest.mark.parametrize("B,T,Hq,Hkv,d,lo,hi", [
+    (64, 4, 128, 8, 128, 4, 64),       # 512 one-slab units, two per workgroup, 64 query rows: one query area, refilled between units
+    (5, 3, 24, 6, 128, 3, 700),        # 9 query rows; units of 1 .. 11 slabs, several to a workgroup or one over several
+    (33, 6, 64, 8, 64, 6, 1500),       # 48 query rows at d 64 (two key groups of 64 keys), whole units and pieces mixed
+    (64, 1, 128, 128, 64, 1, 16),      # 8192 units, more than the arrival counters: a workgroup per unit
+    (1, 8, 8, 1, 64, 40000, 40000),    # one unit over every workgroup: 256 pieces
+])
+def test_runs_of_slabs_over_ragged_units(B, T, Hq, Hkv, d, lo, hi, layout):
+    cap = (hi + 7) // 8 * 8
+    q, k, v = _inputs(B, T, Hq, Hkv, d, cap, seed=90 + B)
+    rng = np.random.default_rng(B)
+    length = rng.integers(lo, hi + 1, B).tolist()
+    length[0], length[-1] = lo, hi
+    for _ in range(2):   # the second call finds the counters the first left
+        out, lse = _run(q, k, v, length, layout)
+    _check(q, k, v, length, out, lse)
