@@ -682,6 +682,33 @@ static int decode_nsub(int units, int n_max, int G, int d, int dtype) {
     return wide ? 2 : 1;
 }
 
+// Whether a launch runs as slabs dealt evenly to one workgroup per CU with
+// matrix-core products (stream_kernel) instead of the split kernel above, which
+// starts and ends sooner (6.0 us against 8.5 for one sequence of 2000 keys, 8
+// KV heads, d 64) and does as well on even batches at head_dim 64.  bf16 only.
+// Measured (split -> stream, us; Hkv 8 unless given):
+//   G 16: the vector-ALU products bound the split kernel (2 KV heads, 2000 keys:
+//     12.3 -> 9.2 at d 64, 22.5 -> 11.5 at d 128), from a few slabs on;
+//   G 8 or d 128: long launches (G 4, d 128: 8000 keys 15.1 -> 14.1, 32768 keys
+//     42.8 -> 29.0, 16 of 500 .. 3000 keys 40.5 -> 28.9; 4000 keys in all 9.8 -> 10.2);
+//   G <= 4, d 64: ragged batches with units long enough to carry a flush each
+//     (64 of 600 .. 3200 keys 56 -> 50, 16 of 500 .. 3000 19.5 -> 17.7; but 64 of
+//     100 .. 800 18.6 -> 24.3, and 16 of 1500 each 13.3 -> 14.1).
+bool decode_streams(int B, int Hkv, int G, int d, int dtype, const int *n_keys) {
+    if (dtype != MAD_BF16) return false;
+    const int slab = stream_slab(d);
+    int64_t slabs = 0, keys = 0, most = 0;
+    for (int b = 0; b < B; ++b) {
+        slabs += n_keys[b] > 0 ? (n_keys[b] - 1) / slab + 1 : 1;
+        keys += n_keys[b];
+        most = n_keys[b] > most ? n_keys[b] : most;
+    }
+    slabs *= Hkv;
+    if (G == 16) return slabs >= 32;
+    if (G == 8 || d == 128) return slabs >= (d == 128 ? 1024 : 512);
+    return slabs >= (int64_t)8 * B * Hkv && (slabs >= 8192 || (slabs >= 1024 && keys * 10 <= most * B * 7));
+}
+
 DecodePlan plan_decode(int B, int Hkv, int G, int d, int dtype, const int *n_keys) {
     DecodePlan p;
     p.units = B * Hkv;
@@ -741,7 +768,9 @@ size_t decode_part_stride(int d, int G) {
 }
 
 size_t decode_ws_bytes(int B, int Hq, int Hkv, int d) {
-    return kCounterRegionBytes + (size_t)B * Hkv * decode_part_stride(d, Hq / Hkv) * 4 + 256;
+    const size_t splits = (size_t)B * Hkv * decode_part_stride(d, Hq / Hkv) * 4 + 256;
+    const size_t pieces = stream_part_bytes(B * Hkv, Hq / Hkv, d);
+    return kCounterRegionBytes + (splits > pieces ? splits : pieces);
 }
 
 template <typename T, int D, int G, int NSUB>

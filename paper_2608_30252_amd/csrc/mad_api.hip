@@ -147,6 +147,40 @@ int decode_impl(const void *q, int B, int Hq, int Hkv, int d, int dtype, float s
         a.seq[b].w = mode[b];
         n_keys[b] = a.seq[b].x + a.seq[b].y + (mode[b] ? 1 : 0);
     }
+    // long bf16 launches stream; without the workspace that takes they run as the short ones do
+    const size_t part = mad::stream_part_bytes(B * Hkv, G, d);
+    if (mad::decode_streams(B, Hkv, G, d, dtype, n_keys) && ws && aligned16(ws) &&
+        ws_bytes >= mad::kCounterRegionBytes + part) {
+        mad::StreamArgs s;
+        memset(&s, 0, sizeof(s));
+        s.kind = mad::kStreamDraft;
+        s.q = q;
+        s.out = out;
+        s.lse = lse;
+        if (mem) {
+            s.k = mem->k; s.v = mem->v; s.seq = mem->seq_stride; s.head = mem->head_stride;
+        }
+        s.w_cap = 1;
+        if (win) {
+            s.wk = win->k; s.wv = win->v; s.w_seq = win->seq_stride; s.w_head = win->head_stride; s.w_cap = win->cap;
+        }
+        s.kn = k_new;
+        s.vn = v_new;
+        s.part = (float *)((char *)ws + mad::kCounterRegionBytes);
+        s.counters = (unsigned *)ws;
+        s.scale_log2 = scale * 1.4426950408889634f;
+        s.Hq = Hq;
+        s.G = G;
+        s.T = 1;
+        mad::plan_stream(s, B, Hkv, d, n_keys);
+        for (int b = 0; b < B; ++b) {
+            s.row[b].x = a.seq[b].x;
+            s.row[b].y = a.seq[b].y;
+            s.ring[b].x = a.seq[b].z;
+            s.ring[b].y = a.seq[b].w;
+        }
+        return hip_status(mad::launch_stream(s, d, (hipStream_t)stream), "decode launch");
+    }
     mad::DecodePlan p = mad::plan_decode(B, Hkv, G, d, dtype, n_keys);
     size_t need = p.n_splits > 1 ? mad::decode_ws_bytes(B, Hq, Hkv, d) : 0;
     if (need > 0) {
@@ -386,15 +420,12 @@ int verify_impl(const void *q, int B, int T, int Hq, int Hkv, int d, int dtype, 
     a.q = q;
     a.k = k;
     a.v = v;
-    a.vnat = vnat ? 1 : 0;
+    a.kind = vnat ? mad::kStreamRows : mad::kStreamVT;
     a.out = out;
     a.lse = lse;
     a.seq = seq_stride;
     a.head = head_stride;
-    size_t off_o, off_ml;
-    mad::verify_ws_layout(B, Hq, Hkv, d, T, &off_o, &off_ml);
-    a.part = (float *)((char *)ws + off_o);
-    a.part_ml = (float *)((char *)ws + off_ml);
+    a.part = (float *)((char *)ws + mad::kCounterRegionBytes);
     a.counters = (unsigned *)ws;
     a.scale_log2 = scale * 1.4426950408889634f;
     a.cap = cap;

@@ -51,6 +51,7 @@ struct DecodePlan {
     int fold;   // 1: the last split also takes the few keys past n_splits * chunk
 };
 
+bool decode_streams(int B, int Hkv, int G, int d, int dtype, const int *n_keys);
 DecodePlan plan_decode(int B, int Hkv, int G, int d, int dtype, const int *n_keys);
 int decode_max_splits(int d, int G);
 size_t decode_part_stride(int d, int G);
@@ -80,21 +81,31 @@ __host__ __device__ constexpr int stream_slab(int d) { return d == 128 ? 64 : 12
 
 constexpr int kMergeBytes = 128 << 10;   // LDS a merging workgroup fills with pieces at a time
 
+// verify over a cache of K and V rows; over K rows and V^T (one run of cap keys per feature);
+// the draft's decode: memory rows, window ring, new token (T = 1)
+enum { kStreamRows = 0, kStreamVT = 1, kStreamDraft = 2 };
+
 struct StreamArgs {
-    const void *q, *k, *v;    // v: rows of d when vnat, else one run of cap keys per feature
+    const void *q, *k, *v;    // draft: k and v are the memory rows
     void *out;
     float *lse;
     int64_t seq, head;        // element strides of sequences and KV heads (K and V alike)
-    float *part, *part_ml;    // pieces: [T*G][d] unnormalised o, [T*G][2] (max in log2 units, sum)
+    float *part;              // the units' pieces
     unsigned *counters;       // counter region: unit u on line u
     float scale_log2;
-    int cap, Hq, Hkv, G, T, vnat;
+    int cap, Hq, Hkv, G, T, kind;
     int n_wg, base, rem;      // workgroup w runs base (+ 1 for w < rem) consecutive slabs
     int by_unit;              // 1: instead, the workgroups of a row's units split each unit evenly
     int B, merge_nr;          // merge_nr > 0: the pieces are merged by a second launch, merge_nr rows a workgroup
     int rows, wgs;            // slabs, and by_unit workgroups, of one KV head over all rows
     // per row: keys, -, workgroups (by_unit) and slabs of the rows before it (one KV head); past the last row: the end
-    int4 row[kMaxB];
+    int4 row[kMaxB];          // (draft: memory rows, window rows, ...)
+    // draft: the window ring and the new token; per row the ring start and the new-token mode
+    void *wk, *wv;
+    const void *kn, *vn;
+    int64_t w_seq, w_head;
+    int w_cap;
+    int2 ring[kMaxB];
 };
 
 // the first slab of workgroup w's run, and the workgroup whose run holds slab x
@@ -108,7 +119,7 @@ __host__ __device__ inline int stream_owner(int x, int base, int rem) {
 void plan_stream(StreamArgs &a, int B, int Hkv, int d, const int *n_keys);
 hipError_t launch_stream(const StreamArgs &a, int d, hipStream_t st);
 size_t verify_ws_bytes(int B, int Hq, int Hkv, int d, int T);
-void verify_ws_layout(int B, int Hq, int Hkv, int d, int T, size_t *off_o, size_t *off_ml);
+size_t stream_part_bytes(int units, int rows, int d);
 
 // ----------------------------------------------------------------- layer ----
 constexpr int kMaxLinRows = MAD_MAX_LAYER_ROWS;

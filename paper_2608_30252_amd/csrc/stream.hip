@@ -1,7 +1,10 @@
 // stream.hip -- bandwidth-bound bf16 attention over long key/value streams: the
 // target's (gamma+1)-query verify attention over its full KV cache (Sec. 2.1
 // draft-verify paradigm; Sec. 3.3: the verifier keeps the full KV), query t of
-// the T = gamma+1 new tokens seeing rows 0 .. len-T+t.
+// the T = gamma+1 new tokens seeing rows 0 .. len-T+t.  Also the draft's decode
+// attention (decode.hip) where its launch is long or has many query heads per
+// KV head (T = 1; a row's keys are its memory, its window ring and the new
+// token, which is appended).
 //
 // Work decomposition.  A unit is one (sequence, KV head); its query tile is the
 // T*G rows (t, g) -> row t*G + g, padded to 16-row blocks.  The keys of every
@@ -93,7 +96,7 @@ __device__ __forceinline__ v4s_t lds_read_tr16(const unsigned char *p) {
 // miss to host memory once the key stream has swept the L2.  The row records
 // come in the same batch, one per lane, and are taken from there by readlane.
 struct StreamCtx {
-    uint64_t q, k, v, out, lse, part, part_ml, counters;
+    uint64_t q, k, v, out, lse, part, counters;
     int64_t seq, head;
     float cs;
     int cap, Hq, Hkv, G, T, base, rem, by_unit, merge_nr, rows, wgs;   // rows, wgs: slabs and (by_unit) workgroups of one KV head over all rows
@@ -108,15 +111,35 @@ __device__ __forceinline__ StreamCtx load_ctx(const StreamArgs &a) {
     StreamCtx x;
     x.rec = a.row[threadIdx.x & 63];
     x.q = ptr_bits(a.q); x.k = ptr_bits(a.k); x.v = ptr_bits(a.v); x.out = ptr_bits(a.out); x.lse = ptr_bits(a.lse);
-    x.part = ptr_bits(a.part); x.part_ml = ptr_bits(a.part_ml); x.counters = ptr_bits(a.counters);
+    x.part = ptr_bits(a.part); x.counters = ptr_bits(a.counters);
     x.seq = a.seq; x.head = a.head;
     x.cs = a.scale_log2;
     x.cap = a.cap; x.Hq = a.Hq; x.Hkv = a.Hkv; x.G = a.G; x.T = a.T; x.base = a.base; x.rem = a.rem;
     x.by_unit = a.by_unit; x.merge_nr = a.merge_nr; x.rows = a.rows; x.wgs = a.wgs;
-    asm volatile("" : "+s"(x.q), "+s"(x.k), "+s"(x.v), "+s"(x.out), "+s"(x.lse), "+s"(x.part), "+s"(x.part_ml),
+    asm volatile("" : "+s"(x.q), "+s"(x.k), "+s"(x.v), "+s"(x.out), "+s"(x.lse), "+s"(x.part),
                  "+s"(x.counters), "+s"(x.seq), "+s"(x.head), "+s"(x.cs));
     asm volatile("" : "+s"(x.cap), "+s"(x.Hq), "+s"(x.Hkv), "+s"(x.G), "+s"(x.T), "+s"(x.base), "+s"(x.rem),
                  "+s"(x.by_unit), "+s"(x.merge_nr), "+s"(x.rows), "+s"(x.wgs));
+    return x;
+}
+
+// The draft's window ring and new token, and per lane the ring start and the
+// new-token mode of row `lane` (rec.x is then the row's memory length, rec.y
+// its window length).
+struct DraftCtx {
+    uint64_t wk, wv, kn, vn;
+    int64_t seq, head;
+    int cap;
+    int2 rec;
+    __device__ __forceinline__ int start(int b) const { return __builtin_amdgcn_readlane(rec.x, b); }
+    __device__ __forceinline__ int mode(int b) const { return __builtin_amdgcn_readlane(rec.y, b); }
+};
+__device__ __forceinline__ DraftCtx load_draft(const StreamArgs &a) {
+    DraftCtx x;
+    x.rec = a.ring[threadIdx.x & 63];
+    x.wk = ptr_bits(a.wk); x.wv = ptr_bits(a.wv); x.kn = ptr_bits(a.kn); x.vn = ptr_bits(a.vn);
+    x.seq = a.w_seq; x.head = a.w_head; x.cap = a.w_cap;
+    asm volatile("" : "+s"(x.wk), "+s"(x.wv), "+s"(x.kn), "+s"(x.vn), "+s"(x.seq), "+s"(x.head), "+s"(x.cap));
     return x;
 }
 
@@ -134,32 +157,90 @@ __device__ __forceinline__ UnitPieces unit_pieces(const StreamCtx &a, int u) {
     return {w0 + u, stream_owner(s0 + nt - 1, a.base, a.rem) - w0 + 1};
 }
 
-// Log-sum-exp merge of rows [ra, ra + nr) of unit u from its pieces, by a
-// workgroup of 512 threads, in three steps with a barrier after each: the
-// pieces into LDS in one round trip of device-coherent direct loads (o at
-// `so`, 16 bytes aligned, np * nr * D * 4 of them), their (max, sum) beside it;
-// eight lanes per row turn those into weights while the rest arrives; the sums.
-// np * nr <= 512.
+// A piece in the workspace: [R][D] unnormalised o, [R] (max in log2 units, sum),
+// padded to 16 bytes.
+__host__ __device__ constexpr int piece_floats(int R, int d) { return (R * (d + 2) + 3) & ~3; }
+
+__device__ __forceinline__ size_t out_head(const StreamCtx &a, int u, int row) {
+    const int b = u / a.Hkv, c = u - b * a.Hkv, tt = row / a.G;
+    return ((size_t)b * a.T + tt) * a.Hq + (size_t)c * a.G + (row - tt * a.G);
+}
+
+// Log-sum-exp merge of rows [ra, ra + nr) of unit u from its pieces as they lie
+// in LDS, by a workgroup of 512 threads: eight lanes per row turn the pieces'
+// (max, sum) into weights, then (behind a barrier) one thread per feature quad.
+// Piece p's o rows are at so + p * po bytes, its (max, sum) pairs at sm + p * pm.
 template <int D>
 struct MergeJob {
-    int u, p0, np, ra, nr;
-    unsigned char *so;
-    float2 *sml;    // [np][nr]
-    float *sinv;    // [nr]
+    int u, np, ra, nr;
+    unsigned char *so, *sm;
+    int po, pm;
+    float *sinv;   // [nr]
 
-    // the (max, sum) pairs, one a thread
-    __device__ __forceinline__ uint64_t load_ml(const StreamCtx &a) const {
-        const int pp = threadIdx.x / nr;
-        return pp < np ? load_agent64(bits_ptr<const uint64_t>(a.part_ml) + (size_t)(p0 + pp) * (a.T * a.G) + ra + ((int)threadIdx.x - pp * nr)) : 0;
+    __device__ __forceinline__ void weights(const StreamCtx &a) const {
+        for (int r = threadIdx.x >> 3; r < nr; r += 64) {
+            const int l8 = threadIdx.x & 7;
+            float M = -INFINITY, L = 0.f;
+            for (int p = l8; p < np; p += 8) M = fmaxf(M, reinterpret_cast<const float2 *>(sm + p * pm)[r].x);
+            M = group_max<8>(M);
+            const float mr = M == -INFINITY ? 0.f : M;
+            for (int p = l8; p < np; p += 8) {
+                float2 *v = reinterpret_cast<float2 *>(sm + p * pm) + r;
+                const float wt = __builtin_amdgcn_exp2f(v->x - mr);
+                L = fmaf(wt, v->y, L);
+                v->x = wt;
+            }
+            L = group_sum<8>(L);
+            if (l8 == 0) {
+                sinv[r] = L > 0.f ? 1.f / L : 0.f;
+                if (a.lse) bits_ptr<float>(a.lse)[out_head(a, u, ra + r)] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
+            }
+        }
     }
-    __device__ __forceinline__ void load_o(const StreamCtx &a) const {
+    __device__ __forceinline__ void sums(const StreamCtx &a) const {
+        for (int x = threadIdx.x; x < nr * (D / 4); x += 512) {   // feature quad x % (D / 4) of row x / (D / 4)
+            const int r = x / (D / 4);
+            f32x4_v y = f32x4_v{0.f, 0.f, 0.f, 0.f};
+            #pragma unroll 8
+            for (int p = 0; p < np; ++p) {
+                const f32x4_v v = *reinterpret_cast<const f32x4_v *>(so + p * po + x * 16);
+                const float wt = reinterpret_cast<const float2 *>(sm + p * pm)[r].x;
+                #pragma unroll
+                for (int e = 0; e < 4; ++e) y[e] = fmaf(wt, v[e], y[e]);
+            }
+            const float inv = sinv[r];
+            *reinterpret_cast<uint2 *>(bits_ptr<bf16_t>(a.out) + out_head(a, u, ra + r) * D + (x % (D / 4)) * 4) =
+                make_uint2(pack_bf16x2(y[0] * inv, y[1] * inv), pack_bf16x2(y[2] * inv, y[3] * inv));
+        }
+    }
+};
+
+// `bytes` (a multiple of 16) of pieces straight into LDS, whole; lanes past the end read its last 16 bytes
+// again.  The LDS behind is padded to 1 KB.
+__device__ __forceinline__ void load_pieces(const float *src, int bytes, unsigned char *lds) {
+    for (int x = (threadIdx.x >> 6) * 1024; x < bytes; x += 8192)
+        lds_stream16_coherent(reinterpret_cast<const unsigned char *>(src) + min(x + (int)(threadIdx.x & 63) * 16, bytes - 16), lds + x);
+}
+
+// Rows [r0, r1) of unit u where its pieces are more than kMergeBytes: as many
+// rows at a time as fit, sml 4 KB for their (max, sum).
+template <int D>
+__device__ __forceinline__ void merge_rows(const StreamCtx &a, int u, UnitPieces up, int r0, int r1, unsigned char *smem,
+                                           float2 *sml) {
+    __shared__ float sinv[MAD_MAX_VERIFY_ROWS];
+    const int tid = threadIdx.x, R = a.T * a.G, np = up.np, pf = piece_floats(R, D);
+    const float *part = bits_ptr<const float>(a.part) + (size_t)up.p0 * pf;
+    const int most = kMergeBytes / (np * D * 4);   // at least 1: np <= kStreamWGs
+    for (int ra = r0; ra < r1; ra += most) {
+        const int nr = min(most, r1 - ra), q = nr * (D / 4), total = np * q, dp = 512 / q, dx = 512 - dp * q;
+        const int mp = tid / nr;   // the (max, sum) pairs, one a thread: np * nr <= 512
+        const uint64_t ml = mp < np ? load_agent64(reinterpret_cast<const uint64_t *>(part + (size_t)mp * pf + R * D) + ra + (tid - mp * nr)) : 0;
+        __syncthreads();   // earlier readers of smem and sml are done
         // 16-byte chunk x of [np][q]: x and its (piece, offset) advance by 512 a step; the last step's surplus lanes read the last chunk
-        const int tid = threadIdx.x, R = a.T * a.G, q = nr * (D / 4), total = np * q, dp = 512 / q, dx = 512 - dp * q;
-        const float *po = bits_ptr<const float>(a.part) + (size_t)p0 * R * D;
         int pc = tid / q, off = tid - pc * q;
         for (int x0 = tid & ~63; x0 < total; x0 += 512) {
             const bool in = pc < np;
-            lds_stream16_coherent(po + ((size_t)(in ? pc : np - 1) * R + ra) * D + (in ? off : q - 1) * 4, so + x0 * 16);
+            lds_stream16_coherent(part + (size_t)(in ? pc : np - 1) * pf + ra * D + (in ? off : q - 1) * 4, smem + x0 * 16);
             pc += dp;
             off += dx;
             if (off >= q) {
@@ -167,66 +248,9 @@ struct MergeJob {
                 ++pc;
             }
         }
-    }
-    __device__ __forceinline__ void store_ml(uint64_t v) const {
-        if ((int)threadIdx.x < np * nr) sml[threadIdx.x] = make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
-    }
-    __device__ __forceinline__ size_t head(const StreamCtx &a, int r) const {
-        const int b = u / a.Hkv, c = u - b * a.Hkv, row = ra + r, tt = row / a.G;
-        return ((size_t)b * a.T + tt) * a.Hq + (size_t)c * a.G + (row - tt * a.G);
-    }
-    __device__ __forceinline__ void weights(const StreamCtx &a) const {
-        for (int r = threadIdx.x >> 3; r < nr; r += 64) {
-            const int l8 = threadIdx.x & 7;
-            float M = -INFINITY, L = 0.f;
-            for (int p = l8; p < np; p += 8) M = fmaxf(M, sml[p * nr + r].x);
-            M = group_max<8>(M);
-            const float mr = M == -INFINITY ? 0.f : M;
-            for (int p = l8; p < np; p += 8) {
-                const float2 v = sml[p * nr + r];
-                const float wt = __builtin_amdgcn_exp2f(v.x - mr);
-                L = fmaf(wt, v.y, L);
-                sml[p * nr + r].x = wt;
-            }
-            L = group_sum<8>(L);
-            if (l8 == 0) {
-                sinv[r] = L > 0.f ? 1.f / L : 0.f;
-                if (a.lse) bits_ptr<float>(a.lse)[head(a, r)] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
-            }
-        }
-    }
-    __device__ __forceinline__ void sums(const StreamCtx &a) const {
-        const int q = nr * (D / 4);
-        for (int x = threadIdx.x; x < q; x += 512) {   // feature quad x % (D / 4) of row x / (D / 4)
-            const int r = x / (D / 4);
-            f32x4_v y = f32x4_v{0.f, 0.f, 0.f, 0.f};
-            #pragma unroll 8
-            for (int p = 0; p < np; ++p) {
-                const f32x4_v v = *reinterpret_cast<const f32x4_v *>(so + (size_t)(p * q + x) * 16);
-                const float wt = sml[p * nr + r].x;
-                #pragma unroll
-                for (int e = 0; e < 4; ++e) y[e] = fmaf(wt, v[e], y[e]);
-            }
-            const float inv = sinv[r];
-            *reinterpret_cast<uint2 *>(bits_ptr<bf16_t>(a.out) + head(a, r) * D + (x % (D / 4)) * 4) =
-                make_uint2(pack_bf16x2(y[0] * inv, y[1] * inv), pack_bf16x2(y[2] * inv, y[3] * inv));
-        }
-    }
-};
-
-// rows [r0, r1) of unit u, as many at a time as fit kMergeBytes of LDS
-template <int D>
-__device__ __forceinline__ void merge_rows(const StreamCtx &a, int u, UnitPieces up, int r0, int r1, unsigned char *smem,
-                                           float2 *sml) {
-    __shared__ float sinv[MAD_MAX_VERIFY_ROWS];
-    const int most = kMergeBytes / (up.np * D * 4);   // at least 1: np <= kStreamWGs
-    for (int ra = r0; ra < r1; ra += most) {
-        const MergeJob<D> j = {u, up.p0, up.np, ra, min(most, r1 - ra), smem, sml, sinv};
-        const uint64_t ml = j.load_ml(a);
-        __syncthreads();   // earlier readers of smem and sml are done
-        j.load_o(a);
-        j.store_ml(ml);
+        if (mp < np) sml[tid] = make_float2(__uint_as_float((uint32_t)ml), __uint_as_float((uint32_t)(ml >> 32)));
         __syncthreads();
+        const MergeJob<D> j = {u, np, ra, nr, smem, reinterpret_cast<unsigned char *>(sml), q * 16, nr * 8, sinv};
         j.weights(a);
         wait_vm(0);
         __syncthreads();
@@ -234,19 +258,21 @@ __device__ __forceinline__ void merge_rows(const StreamCtx &a, int u, UnitPieces
     }
 }
 
-template <int D, int NB, bool VNAT>
+template <int D, int NB, int KIND>
 __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
     using C = StreamCfg<D, NB>;
     constexpr int KST = D / 32, DB = D / 16;
+    constexpr bool VNAT = KIND != kStreamVT, DRAFT = KIND == kStreamDraft;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int s_last[2];
     MAD_TRACE_T0();
     const StreamCtx a = load_ctx(args);
+    const DraftCtx ring = DRAFT ? load_draft(args) : DraftCtx{};
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lr = lane & 15, lg = lane >> 4;
     const int w = blockIdx.x;
-    const int T = a.T, G = a.G, R = T * G, Hkv = a.Hkv;
+    const int T = DRAFT ? 1 : a.T, G = a.G, R = T * G, Hkv = a.Hkv;
 
     // ---- this workgroup's run of slabs: the first one's unit (b, c) and slab t, and their number ----
     int b, c, t, left;
@@ -273,9 +299,22 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
     int i_stage = 0;                            // stage of the slab, bytes
     int64_t i_keys = 0;                         // the unit's keys from the slab on
     const bf16_t *i_k = nullptr, *i_v = nullptr;   // the slab's K and V rows (V^T: the unit's first feature)
+    // draft: the unit's memory and window lengths, ring start, ring rows and new token
+    int i_mlen = 0, i_wlen = 0, i_wst = 0;
+    const bf16_t *i_wk = nullptr, *i_wv = nullptr;
+    auto keys_of = [&](int row) {
+        return DRAFT ? a.len(row) + __builtin_amdgcn_readlane(a.rec.y, row) + (ring.mode(row) != 0 ? 1 : 0) : a.len(row);
+    };
     auto i_unit = [&]() {
         i_nt = a.slabs(i_b);
-        i_keys = a.len(i_b) - (int64_t)i_t * C::SLAB;
+        if constexpr (DRAFT) {
+            i_mlen = a.len(i_b);
+            i_wlen = __builtin_amdgcn_readlane(a.rec.y, i_b);
+            i_wst = ring.start(i_b);
+            i_wk = bits_ptr<const bf16_t>(ring.wk) + i_b * ring.seq + i_c * ring.head;
+            i_wv = bits_ptr<const bf16_t>(ring.wv) + i_b * ring.seq + i_c * ring.head;
+        }
+        i_keys = keys_of(i_b) - (int64_t)i_t * C::SLAB;
         i_k = bits_ptr<const bf16_t>(a.k) + i_b * a.seq + i_c * a.head + (int64_t)i_t * C::SLAB * D;
         i_v = bits_ptr<const bf16_t>(a.v) + i_b * a.seq + i_c * a.head + (VNAT ? (int64_t)i_t * C::SLAB * D : 0);
     };
@@ -292,7 +331,7 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
         v_off[j] = kr * C::RB + ((slot ^ vn_swz(kr)) << 4) - 1024 * j;
     }
     static_assert(LPW == 2, "lds_stream16_nt_x2");
-    const uint32_t ring = __builtin_amdgcn_readfirstlane(lds_addr(smem)) + wv * LPW * 1024;
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(smem)) + wv * LPW * 1024;
     // the first slab of a unit (or of the run) needs a free query area
     auto can_issue = [&]() {
         return i_left > 0 && ((i_t > 0 && issued > 0) || q_issued - q_done < C::QSLOTS);
@@ -308,9 +347,45 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
             }
             ++q_issued;
         }
-        if (VNAT && i_keys >= C::SLAB) {   // every row of the slab exists: one base and fixed lane offsets
-            lds_stream16_nt_x2(i_k, k_off[0], k_off[1], ring + i_stage);
-            lds_stream16_nt_x2(i_v, v_off[0], v_off[1], ring + i_stage + C::KBYTES);
+        // a slab whose rows all exist in one place (draft: in the memory, or in the ring without a
+        // wrap) has one base and fixed lane offsets
+        const bf16_t *k0 = i_k, *v0 = i_v;
+        bool one = VNAT && i_keys >= C::SLAB;
+        if constexpr (DRAFT) {
+            const int kb = i_t * C::SLAB;
+            one = kb + C::SLAB <= i_mlen;
+            if (!one && kb >= i_mlen && kb + C::SLAB <= i_mlen + i_wlen) {
+                int r0 = i_wst + (kb - i_mlen);
+                if (r0 >= ring.cap) r0 -= ring.cap;
+                one = r0 + C::SLAB <= ring.cap;
+                k0 = i_wk + (size_t)r0 * D;
+                v0 = i_wv + (size_t)r0 * D;
+            }
+        }
+        if (one) {
+            lds_stream16_nt_x2(k0, k_off[0], k_off[1], lds0 + i_stage);
+            lds_stream16_nt_x2(v0, v_off[0], v_off[1], lds0 + i_stage + C::KBYTES);
+        } else if constexpr (DRAFT) {
+            // row by row: memory, ring, the new token; rows past the end repeat the last one (masked),
+            // those of an empty row read the queries (never used)
+            unsigned char *st = smem + i_stage;
+            const int n = keys_of(i_b);
+            #pragma unroll
+            for (int j = 0; j < LPW; ++j) {
+                const int inst = wv * LPW + j;
+                const int cidx = inst * 64 + lane, kr = cidx / C::CPR, slot = cidx % C::CPR;
+                const int key = min(i_t * C::SLAB + kr, n - 1), i = key - i_mlen;
+                int r = i_wst + i;
+                if (r >= ring.cap) r -= ring.cap;
+                const size_t nrow = ((size_t)i_b * Hkv + i_c) * D;
+                const bf16_t *kp = i < 0 ? i_k + (int64_t)(key - i_t * C::SLAB) * D
+                                 : i < i_wlen ? i_wk + (size_t)r * D : bits_ptr<const bf16_t>(ring.kn) + nrow;
+                const bf16_t *vp = i < 0 ? i_v + (int64_t)(key - i_t * C::SLAB) * D
+                                 : i < i_wlen ? i_wv + (size_t)r * D : bits_ptr<const bf16_t>(ring.vn) + nrow;
+                if (n == 0) kp = vp = bits_ptr<const bf16_t>(a.q);
+                lds_stream16_nt(kp + (slot ^ vk_swz(kr)) * 8, st + inst * 1024);
+                lds_stream16_nt(vp + (slot ^ vn_swz(kr)) * 8, st + C::KBYTES + inst * 1024);
+            }
         } else {
             unsigned char *st = smem + i_stage;
             const int keys = (int)min(i_keys, (int64_t)C::SLAB);
@@ -360,7 +435,7 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
 
     auto start_unit = [&]() {
         nt = a.slabs(b);
-        len = a.len(b);
+        len = keys_of(b);
         lim = len - T + row_t;
         const unsigned char *qa = smem + C::OFF_Q + (C::QSLOTS == 2 ? (q_done & 1) * C::QBYTES : 0) + min(row, R - 1) * C::RB;
         #pragma unroll
@@ -484,6 +559,20 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
         constexpr int DP = D / C::XPASS, QP = DP / 4;                 // features, chunks of a row per pass
         float2 *xml = reinterpret_cast<float2 *>(smem + C::OFF_ML);   // [KS][RP]
         const float lt = sum_over_row_lanes(l_run);
+        if constexpr (DRAFT) {
+            // the unit's last slab holds the new token: append it to the window ring from here
+            // (its row is outside every window of the launch)
+            if (t == nt && ring.mode(b) == 2 && tid < 2 * C::CPR) {
+                const int kr = len - 1 - (nt - 1) * C::SLAB, ch = tid % C::CPR;
+                const bool is_v = tid >= C::CPR;
+                const uint4 x = *reinterpret_cast<const uint4 *>(st + (is_v ? C::KBYTES : 0) + kr * C::RB +
+                                                                 ((ch ^ (is_v ? vn_swz(kr) : vk_swz(kr))) << 4));
+                int r = ring.start(b) + __builtin_amdgcn_readlane(a.rec.y, b);
+                if (r >= ring.cap) r -= ring.cap;
+                bf16_t *dst = bits_ptr<bf16_t>(is_v ? ring.wv : ring.wk) + b * ring.seq + c * ring.head + (size_t)r * D;
+                reinterpret_cast<uint4 *>(dst)[ch] = x;
+            }
+        }
         #pragma unroll
         for (int ps = 0; ps < C::XPASS; ++ps) {
             __syncthreads();   // every wave is done with the stage
@@ -516,14 +605,15 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
                     const int tt = r / G;
                     const size_t head = ((size_t)b * T + tt) * a.Hq + (size_t)c * G + (r - tt * G);
                     const float inv = L > 0.f ? 1.f / L : 0.f;
-                    *reinterpret_cast<uint2 *>(bits_ptr<bf16_t>(a.out) + head * D + ps * DP + ch * 4) =
-                        make_uint2(pack_bf16x2(y[0] * inv, y[1] * inv), pack_bf16x2(y[2] * inv, y[3] * inv));
+                    uint2 pk = make_uint2(pack_bf16x2(y[0] * inv, y[1] * inv), pack_bf16x2(y[2] * inv, y[3] * inv));
+                    if (L == 0.f) pk = make_uint2(0u, 0u);   // no key at all: whatever rows stood in
+                    *reinterpret_cast<uint2 *>(bits_ptr<bf16_t>(a.out) + head * D + ps * DP + ch * 4) = pk;
                     if (lse && ps == 0 && ch == 0) lse[head] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
                 } else {
                     // workgroups and units both advance in slab order, so w + u numbers the pieces one after the other
-                    const size_t pr = (size_t)(w + u) * R + r;
-                    store_agent4(bits_ptr<float>(a.part) + pr * D + ps * DP + ch * 4, y);
-                    if (ps == 0 && ch == 0) store_agent2(bits_ptr<float>(a.part_ml) + pr * 2, M, L);
+                    float *pp = bits_ptr<float>(a.part) + (size_t)(w + u) * piece_floats(R, D);
+                    store_agent4(pp + r * D + ps * DP + ch * 4, y);
+                    if (ps == 0 && ch == 0) store_agent2(pp + R * D + 2 * r, M, L);
                 }
             }
         }
@@ -567,11 +657,12 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
     MAD_TRACE(mad_trace_verify, 1);
     if ((pu0 < 0 && pu1 < 0) || a.merge_nr > 0) return;
 
-    // ---- arrivals; the last workgroup at a unit merges its pieces ----
+    // ---- arrivals; the last workgroup at a unit merges its pieces, both of its units' (where it is
+    // last at both) behind one round trip ----
+    const UnitPieces up0 = unit_pieces(a, max(pu0, 0)), up1 = unit_pieces(a, max(pu1, 0));
     wait_vm_stores();
     __syncthreads();
     MAD_TRACE(mad_trace_verify, 2);
-    const UnitPieces up0 = unit_pieces(a, max(pu0, 0)), up1 = unit_pieces(a, max(pu1, 0));
     if (tid == 0 || tid == 64) {
         const int u = tid == 0 ? pu0 : pu1;
         int last = 0;
@@ -584,27 +675,29 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
     }
     __syncthreads();
     MAD_TRACE(mad_trace_verify, 3);
+    const int pf = piece_floats(R, D);
+    const float *part = bits_ptr<const float>(a.part);
     float2 *sml = reinterpret_cast<float2 *>(smem + C::OFF_Q);
-    if (s_last[0] && s_last[1] && (up0.np + up1.np) * R * D * 4 <= kMergeBytes) {
-        // last at both of its units: both merges behind one round trip
+    const int last = (s_last[0] ? 1 : 0) + (s_last[1] ? 2 : 0);
+    if (last == 0) return;
+    const int bytes0 = (last & 1) ? up0.np * pf * 4 : 0, bytes1 = (last & 2) ? up1.np * pf * 4 : 0;
+    const int at1 = (bytes0 + 1023) & ~1023;
+    if (at1 + bytes1 <= kMergeBytes) {
         __shared__ float sinv[2 * MAD_MAX_VERIFY_ROWS];
-        const MergeJob<D> j0 = {pu0, up0.p0, up0.np, 0, R, smem, sml, sinv};
-        const MergeJob<D> j1 = {pu1, up1.p0, up1.np, 0, R, smem + up0.np * R * D * 4, sml + up0.np * R, sinv + R};
-        const uint64_t ml0 = j0.load_ml(a), ml1 = j1.load_ml(a);
-        j0.load_o(a);
-        j1.load_o(a);
-        j0.store_ml(ml0);
-        j1.store_ml(ml1);
-        __syncthreads();
-        j0.weights(a);
-        j1.weights(a);
+        if (last & 1) load_pieces(part + (size_t)up0.p0 * pf, bytes0, smem);
+        if (last & 2) load_pieces(part + (size_t)up1.p0 * pf, bytes1, smem + at1);
+        const MergeJob<D> j0 = {pu0, up0.np, 0, R, smem, smem + R * D * 4, pf * 4, pf * 4, sinv};
+        const MergeJob<D> j1 = {pu1, up1.np, 0, R, smem + at1, smem + at1 + R * D * 4, pf * 4, pf * 4, sinv + R};
         wait_vm(0);
         __syncthreads();
-        j0.sums(a);
-        j1.sums(a);
+        if (last & 1) j0.weights(a);
+        if (last & 2) j1.weights(a);
+        __syncthreads();
+        if (last & 1) j0.sums(a);
+        if (last & 2) j1.sums(a);
     } else {
-        if (s_last[0]) merge_rows<D>(a, pu0, up0, 0, R, smem, sml);
-        if (s_last[1]) merge_rows<D>(a, pu1, up1, 0, R, smem, sml);
+        if (last & 1) merge_rows<D>(a, pu0, up0, 0, R, smem, sml);
+        if (last & 2) merge_rows<D>(a, pu1, up1, 0, R, smem, sml);
     }
     MAD_TRACE(mad_trace_verify, 4);
 }
@@ -631,8 +724,9 @@ __global__ __launch_bounds__(512, 1) void stream_merge_kernel(const StreamArgs a
 //   runs      equal contiguous runs over all units in unit order, for ragged
 //             batches whose pieces would come out uneven.
 // A run that crosses into the next unit stalls once (the flush, 1.6 us at 48
-// rows, d 128) and units get one piece more, so by unit is taken up to 1/16
-// above the even share: 4 sequences of 32773 keys (513 slabs a unit) took
+// rows, d 128) and units get one piece more, so by unit is taken up to 2 slabs
+// and 1/16 above the even share: the draft's 16 sequences of 700 .. 1500 keys
+// took 15.4 us in runs of 4 or 5 slabs, 13.4 by unit with 6; 4 sequences of 32773 keys (513 slabs a unit) took
 // 88.7 us in runs, 87.1 by unit; 16 of 600 .. 12000 keys 74 us in runs (100 with
 // splits of one length).  By unit also serves launches with more units than workgroups can
 // count (a unit each: no pieces, no counters).
@@ -660,7 +754,7 @@ void plan_stream(StreamArgs &a, int B, int Hkv, int d, const int *n_keys) {
     int np_max = 1;
     const int even = a.base + (a.rem > 0 ? 1 : 0);
     a.by_unit = 0;
-    for (int share = whole ? nt_max : even; whole || share <= even + even / 16; share += 1 + even / 64) {
+    for (int share = whole ? nt_max : even; whole || share <= even + 2 + even / 16; share += 1 + even / 64) {
         int wgs = 0;
         np_max = 1;
         for (int b = 0; b < B; ++b) {
@@ -683,40 +777,40 @@ void plan_stream(StreamArgs &a, int B, int Hkv, int d, const int *n_keys) {
     // a unit in np pieces merges np T G d floats.  Up to two LDS fulls the last workgroup there does it
     // in the launch (4 us at 10 pieces of 20 rows, d 128); more are spread over a second launch (5.8 us at
     // 33 pieces of 40 rows, six LDS fulls)
-    const int64_t bytes = (int64_t)np_max * a.T * a.G * d * 4;
+    const int64_t bytes = (int64_t)np_max * piece_floats(a.T * a.G, d) * 4;
     a.merge_nr = bytes > 2 * kMergeBytes ? kMergeBytes / (np_max * d * 4) / 4 + 1 : 0;
 }
 
-// pieces: at most one per workgroup and unit boundary
+// the pieces of a launch's units: at most one per workgroup and unit
+size_t stream_part_bytes(int units, int rows, int d) {
+    return align256(((size_t)units + kStreamWGs) * piece_floats(rows, d) * 4);
+}
+
 size_t verify_ws_bytes(int B, int Hq, int Hkv, int d, int T) {
-    size_t off_o, off_ml;
-    verify_ws_layout(B, Hq, Hkv, d, T, &off_o, &off_ml);
-    const size_t pieces = (size_t)B * Hkv + kStreamWGs, rows = (size_t)T * (Hq / Hkv);
-    const size_t bf = off_ml + align256(pieces * rows * 2 * 4);
+    const size_t bf = kCounterRegionBytes + stream_part_bytes(B * Hkv, T * (Hq / Hkv), d);
     // fp32 verify runs the decode kernel once per sequence, its T query rows as the rows
     const size_t f32 = decode_ws_bytes(T, Hq, Hkv, d);
     return bf > f32 ? bf : f32;
 }
 
-void verify_ws_layout(int B, int Hq, int Hkv, int d, int T, size_t *off_o, size_t *off_ml) {
-    const size_t pieces = (size_t)B * Hkv + kStreamWGs, rows = (size_t)T * (Hq / Hkv);
-    *off_o = kCounterRegionBytes;
-    *off_ml = kCounterRegionBytes + align256(pieces * rows * d * 4);
-}
-
 template <int D, int NB>
 static hipError_t launch_nb(const StreamArgs &a, hipStream_t st) {
-    const dim3 grid((unsigned)a.n_wg), block(64 * StreamCfg<D, NB>::NWV);
-    if (a.vnat)
-        hipLaunchKernelGGL((stream_kernel<D, NB, true>), grid, block, (StreamCfg<D, NB>::SMEM), st, a);
-    else
-        hipLaunchKernelGGL((stream_kernel<D, NB, false>), grid, block, (StreamCfg<D, NB>::SMEM), st, a);
+    using C = StreamCfg<D, NB>;
+    const dim3 grid((unsigned)a.n_wg), block(64 * C::NWV);
+    if (a.kind == kStreamRows)
+        hipLaunchKernelGGL((stream_kernel<D, NB, kStreamRows>), grid, block, C::SMEM, st, a);
+    else if (a.kind == kStreamVT)
+        hipLaunchKernelGGL((stream_kernel<D, NB, kStreamVT>), grid, block, C::SMEM, st, a);
+    else if constexpr (NB == 1)
+        hipLaunchKernelGGL((stream_kernel<D, NB, kStreamDraft>), grid, block, C::SMEM, st, a);
     return hipGetLastError();
 }
 
 template <int D>
 static hipError_t launch_d(const StreamArgs &a, hipStream_t st) {
-    switch ((a.T * a.G + 15) / 16) {
+    const int nb = (a.T * a.G + 15) / 16;
+    if (a.kind == kStreamDraft && nb != 1) return hipErrorInvalidValue;
+    switch (nb) {
         case 1: return launch_nb<D, 1>(a, st);
         case 2: return launch_nb<D, 2>(a, st);
         case 3: return launch_nb<D, 3>(a, st);

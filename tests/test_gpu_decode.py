@@ -249,6 +249,22 @@ def test_deterministic():
     assert torch.equal(a[1], b[1])
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,d,mlen,wlen,wcap,wstart,new,mem", [
+    # 16 query heads per KV head: slabs from 32 of them on; rows of 1 .. 9 slabs, an empty row, a window that
+    # wraps, one that ends at the ring's end, one of no rows, ends on and beside a slab's edge
+    (7, 32, 2, 64, [0, 128, 300, 1000, 0, 255, 40], [0, 200, 120, 90, 127, 0, 200], 201, [0, 100, 81, 0, 3, 7, 1], False, True),
+    (7, 32, 2, 128, [0, 64, 300, 500, 0, 127, 40], [0, 63, 120, 90, 127, 0, 200], 201, [0, 100, 81, 0, 3, 7, 1], True, True),
+    # few query heads: ragged, 1024 or more slabs, at least eight a unit on average (d 64)
+    (9, 32, 8, 64, [2900, 100, 3000, 900, 2000, 1300, 700, 2400, 500], 1023, 1060, [1059, 5, 30, 40, 700, 37, 36, 0, 1], True, True),
+    # even batches at head_dim 128: by unit; no memory, the whole prefix in the window
+    (4, 32, 8, 128, [0] * 4, [2300, 2240, 2303, 2304], 2400, [0, 2399, 100, 95], True, False),
+    (8, 64, 8, 128, [1500, 10, 3000, 800, 20, 2000, 64, 1984], 127, 130, [120, 3, 2, 0, 129, 64, 65, 1], True, True),
+])
+def test_long_and_many_headed_launches_stream(B, Hq, Hkv, d, mlen, wlen, wcap, wstart, new, mem):
+    for _ in range(2):   # the second call finds the counters the first left
+        _case(torch.bfloat16, B, Hq, Hkv, d, mlen, wlen, wcap, wstart, new=new, seed=40 + d + B, mem=mem)
+
+
 def test_one_workspace_serves_calls_of_different_shapes():
     """Calls of different shapes share one workspace: counters must never sit
     where another shape's call wrote split partials."""
