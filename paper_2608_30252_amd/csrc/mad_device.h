@@ -324,16 +324,42 @@ __device__ __forceinline__ void lds_stream16_coherent(const void *src, void *lds
 // Two streaming loads of a wave from a wave-uniform base with a 32-bit byte
 // offset per lane, to LDS address `lds` (wave-uniform) and the 1024 bytes after
 // it; the second load's instruction offset adds 1024 to its memory address too.
-__device__ __forceinline__ void lds_stream16_nt_x2(const void *base, uint32_t off0, uint32_t off1, uint32_t lds) {
+// NT: the non-temporal hint.
+template <bool NT>
+__device__ __forceinline__ void lds_stream16_x2(const void *base, uint32_t off0, uint32_t off1, uint32_t lds) {
     const uint32_t m = __builtin_amdgcn_readfirstlane(lds);
     uint64_t b = (uint64_t)(uintptr_t)base;
     b = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)) << 32) |
         (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b);
     uint32_t saved;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3 nt\n\t"
-                 "global_load_lds_dwordx4 %2, %3 offset:1024 nt\n\ts_mov_b32 m0, %0"
-                 : "=&s"(saved) : "v"(off0), "v"(off1), "s"(b), "s"(m) : "memory");
+    if constexpr (NT)
+        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3 nt\n\t"
+                     "global_load_lds_dwordx4 %2, %3 offset:1024 nt\n\ts_mov_b32 m0, %0"
+                     : "=&s"(saved) : "v"(off0), "v"(off1), "s"(b), "s"(m) : "memory");
+    else
+        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\t"
+                     "global_load_lds_dwordx4 %2, %3 offset:1024\n\ts_mov_b32 m0, %0"
+                     : "=&s"(saved) : "v"(off0), "v"(off1), "s"(b), "s"(m) : "memory");
 }
+// Swizzles of the K and V rows of a key tile in LDS (rows of D bf16): 16-byte
+// chunk c of key row k sits at chunk c ^ swz(k), so that both operand reads of
+// the matrix-core attention are free of bank conflicts (64 banks of 4 bytes).
+//   K, ds_read_b128: lane (lr, lg) reads chunk 4 ks + lg of row 8 (lr / 4) +
+//   lr % 4 (+ 4).  A pass serves lanes 0-3, 12-15, 20-23, 24-27 (and so on): 16
+//   rows and two lg.  At d 64 (128-byte rows) the row's parity and three bits
+//   tell them apart; at d 128 every row starts on bank 0 and it takes four.
+//   V, ds_read_b64_tr_b16: a pass of 32 lanes covers two adjacent chunks of rows
+//   8 lg + {0..3} for two lg: eight (row, chunk pair) slots of 32 bytes.
+// With three (K) and k % 4 (V) bits only, as before, d 128 lost a third of its
+// LDS cycles to conflicts and d 64 a quarter.
+template <int D> __device__ __forceinline__ int k_swz(int k) {
+    const int s = (k & 3) | (((k >> 3) & 1) << 2);
+    return D == 64 ? s : s | ((((k >> 3) ^ (k >> 4)) & 1) << 3);
+}
+template <int D> __device__ __forceinline__ int v_swz(int k) {
+    return ((k & 3) << 1) ^ (((k >> 3) & 1) << (D == 64 ? 1 : 3));
+}
+
 // Load N dwords at a wave-uniform address through the scalar cache (s_load).
 template <int N>
 __device__ __forceinline__ void load_uniform_dwords(const void *p, uint32_t (&out)[N]) {

@@ -20,24 +20,37 @@
 // and a block of query tokens; its rows are (token, query head of the GQA
 // group) pairs in 16-token blocks, each wave holding NB of them with their
 // query fragments in registers for the whole pass.  Keys stream in 64-key
-// tiles through two LDS stages, loaded into registers one tile ahead:
-//   * K rows are stored with their 16-byte chunks XOR-swizzled so the A
-//     operand reads of S^T = K Q^T are conflict-free; the A rows are permuted
-//     so that each lane's S^T accumulators hold the 8 consecutive keys that
-//     the PV product's B operand needs (no shuffle of probabilities);
-//   * V rows are stored as they are (16-byte chunks XOR-swizzled by row), and
-//     the A operand of O^T = V^T P^T -- 8 consecutive keys of one feature --
-//     comes from two transposing LDS reads (ds_read_b64_tr_b16: lane 4e + a of
-//     a 16-lane group names features 4a .. 4a+3 of key row e, and lane 4a + b
+// tiles through two LDS stages, the next tile's direct loads
+// (global_load_lds_dwordx4) in flight while one is used:
+//   * K rows land with their 16-byte chunks XOR-swizzled so the A operand reads
+//     of S^T = K Q^T are conflict-free; the A rows are permuted so that each
+//     lane's S^T accumulators hold the 8 consecutive keys that the PV product's
+//     B operand needs (no shuffle of probabilities);
+//   * V rows land as they are (16-byte chunks XOR-swizzled by row), and the A
+//     operand of O^T = V^T P^T -- 8 consecutive keys of one feature -- comes
+//     from two transposing LDS reads (ds_read_b64_tr_b16: lane 4e + a of a
+//     16-lane group names features 4a .. 4a+3 of key row e, and lane 4a + b
 //     receives feature 4a + b of the four rows);
-//   * online softmax per query row (16 scores per lane per tile, two
-//     cross-lane lane swaps), masks applied in place on edge tiles only, and
-//     a lazy rescale: the reference maximum of a row block moves only when a
-//     row gains more than 2^8, so most tiles skip the exponential of the
-//     correction and the rescale of o; one barrier per tile.
+//   * online softmax per query row without a running maximum: probabilities are
+//     taken against the row's reference maximum as it stands, and only when a
+//     lane's sum of 8 exceeds 16 (some row has outgrown its reference by 2 .. 16
+//     times) do the maxima move, o and l rescale and the step's probabilities
+//     get taken again.  Masks apply in place, on the tiles that are not inside
+//     every row's range; one barrier per tile.
+// What bounds it at d 64: vector issue.  A 64-key tile of a wave takes 32 matrix
+// products, 32 fma, 32 exponentials (four issue slots each), 32 adds and 16
+// conversions, and nothing else of weight: no maxima (a fifth of the vector work
+// before), no address arithmetic (stage and half are instruction offsets), no
+// staging registers (128 registers: four waves per SIMD instead of three).
+// 32K prefix, 32/8 heads, 2048 slots: 792 -> 639 us; 4 ragged prefixes at d 128,
+// W 128: 492 -> 411 us (two waves per SIMD there: latency-bound).  Measured
+// and not kept: 64 rows per wave (685 us against 703 on long windows, but twice the time
+// with one query head per KV head), 32-key tiles in three stages at d 128 (419 - 426).
 // Query blocks of every unit are dealt round-robin over the units (with a
 // multiple of 8 units all blocks of one KV head share an XCD and its L2), the
 // heaviest blocks first.
+#include <type_traits>
+
 #include "mad_device.h"
 #include "mad_internal.h"
 
@@ -56,17 +69,9 @@ struct PrefillCfg {
     static constexpr int KTILE = KT * RB;              // K tile bytes
     static constexpr int STAGE = 2 * KTILE;            // K tile + V tile (same size)
     static constexpr int SMEM = 2 * STAGE;
-    static constexpr int KCH = KT * CPR / 256;         // K chunks per thread per tile
-    static constexpr int VCH = KCH;                    // V chunks per thread per tile
+    static constexpr int LPW = KTILE / 1024 / 4;       // K (and V) loads per wave per tile
 };
 
-// swizzle of K row k's 16-byte chunks: distinct for the 8 rows one group of
-// eight lanes reads (k mod 4 and bit 3 of k vary across them)
-__device__ __forceinline__ int k_swz(int k) { return (k & 3) | (((k >> 3) & 1) << 2); }
-// swizzle of V row k's 16-byte chunks: a transposing read of 16 lanes covers
-// rows k0 .. k0+3 (k0 a multiple of 4) x two adjacent chunks; XOR with
-// 2 (k mod 4) spreads the eight (row, chunk) pairs over distinct banks
-__device__ __forceinline__ int v_swz(int k) { return (k & 3) << 1; }
 typedef short v4s_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ v4s_t lds_read_tr16(const unsigned char *p) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s_t *)(p));
@@ -88,16 +93,23 @@ __device__ __forceinline__ float prefill_row_sum(float v) {
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-constexpr float kLazyLog2 = 8.f;   // rescale threshold of the online softmax, log2 units
+constexpr float kLazySum = 16.f;  // rescale threshold of the online softmax: a lane's sum of 8 probabilities
+constexpr float kNoMax = 3e38f;   // minus the reference maximum (log2 units) of a row without keys: 2^(s + this) overflows
+
+// the largest value of the wave, wave-uniform
+__device__ __forceinline__ int wave_max_i32(int v) {
+    #pragma unroll
+    for (int x = 1; x < 64; x *= 2) v = max(v, __shfl_xor(v, x));
+    return __builtin_amdgcn_readfirstlane(v);
+}
 
 __device__ __forceinline__ int prefill_slots_after(int t, int S, int ru, int u) {
     return t <= S ? 0 : (t - S) / ru * u;
 }
 
-// Occupancy: three waves per SIMD at head_dim 64 (the compiler then keeps the
-// kernel within 168 registers; measured 8% faster than two), two at 128.
+// Occupancy: four waves per SIMD at head_dim 64 (128 registers), two at 128.
 template <int D, int G, int NB>
-__global__ __launch_bounds__(256, NB == 2 ? (D == 64 ? 3 : 2) : 1) void prefill_kernel(const PrefillArgs a) {
+__global__ __launch_bounds__(256, D == 64 ? 4 : 2) void prefill_kernel(const PrefillArgs a) {
     using C = PrefillCfg<D>;
     constexpr int KST = D / 32, DB = D / 16;
     constexpr int TBW = 4 * NB / G;   // 16-token blocks per workgroup
@@ -168,11 +180,7 @@ __global__ __launch_bounds__(256, NB == 2 ? (D == 64 ? 3 : 2) : 1) void prefill_
         }
     }
 
-    // ---- tile loader: registers one tile ahead, then LDS ----
-    // one tile's K and V chunks of this thread, staged in registers
-    struct StageRegs {
-        uint4 k[C::KCH], v[C::VCH];
-    };
+    // ---- tile loader: direct loads into LDS, the next tile's into the idle stage ----
     auto tile_base = [&](int t, bool &is_mem, int &end) -> int {
         is_mem = t < n_mem_t;
         if (is_mem) {
@@ -182,158 +190,190 @@ __global__ __launch_bounds__(256, NB == 2 ? (D == 64 ? 3 : 2) : 1) void prefill_
         end = raw_hi;
         return raw_lo + (t - n_mem_t) * C::KT;
     };
-    auto load_regs = [&](int t) -> StageRegs {
-        StageRegs r;
+    // Wave load inst = LPW wave + j brings 1 KB: lane l's LDS slot is chunk cidx % CPR of row cidx / CPR
+    // (cidx = 64 inst + l), which holds the row's chunk slot ^ swizzle(row).  A pair's second load adds
+    // 1024 to both of its addresses (an instruction offset), so its lane offset leaves that out.
+    const int wv = __builtin_amdgcn_readfirstlane(wave);
+    uint32_t k_off[C::LPW], v_off[C::LPW];
+    #pragma unroll
+    for (int j = 0; j < C::LPW; ++j) {
+        const int cidx = (wave * C::LPW + j) * 64 + lane, row = cidx / C::CPR, slot = cidx % C::CPR;
+        k_off[j] = row * C::RB + ((slot ^ k_swz<D>(row)) << 4) - 1024 * (j & 1);
+        v_off[j] = row * C::RB + ((slot ^ v_swz<D>(row)) << 4) - 1024 * (j & 1);
+    }
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(smem)) + wv * C::LPW * 1024;
+    auto load_tile = [&](int t, auto stage_const) {
+        constexpr int ST = decltype(stage_const)::value * C::STAGE;
         bool is_mem;
         int end;
         const int base = tile_base(t, is_mem, end);
-        const bf16_t *ks = is_mem ? mk : rk, *vs = is_mem ? mv : rv;
-        #pragma unroll
-        for (int i = 0; i < C::KCH; ++i) {
-            const int idx = tid + 256 * i, row = idx / C::CPR, ch = idx % C::CPR;
-            const int key = min(base + row, end - 1);   // rows past the range load a valid row (masked)
-            r.k[i] = *reinterpret_cast<const uint4 *>(ks + (size_t)key * D + ch * 8);
-        }
-        #pragma unroll
-        for (int i = 0; i < C::VCH; ++i) {
-            const int idx = tid + 256 * i, row = idx / C::CPR, ch = idx % C::CPR;
-            const int key = min(base + row, end - 1);
-            r.v[i] = *reinterpret_cast<const uint4 *>(vs + (size_t)key * D + ch * 8);
-        }
-        return r;
-    };
-    auto store_lds = [&](int stage, const StageRegs &r) {
-        unsigned char *sk = smem + stage * C::STAGE, *sv = sk + C::KTILE;
-        #pragma unroll
-        for (int i = 0; i < C::KCH; ++i) {
-            const int idx = tid + 256 * i, row = idx / C::CPR, ch = idx % C::CPR;
-            *reinterpret_cast<uint4 *>(sk + row * C::RB + ((ch ^ k_swz(row)) << 4)) = r.k[i];
-        }
-        #pragma unroll
-        for (int i = 0; i < C::VCH; ++i) {
-            const int idx = tid + 256 * i, row = idx / C::CPR, ch = idx % C::CPR;
-            *reinterpret_cast<uint4 *>(sv + row * C::RB + ((ch ^ v_swz(row)) << 4)) = r.v[i];
+        const bf16_t *ks = (is_mem ? mk : rk) + (size_t)base * D, *vs = (is_mem ? mv : rv) + (size_t)base * D;
+        if (base + C::KT <= end) {
+            #pragma unroll
+            for (int j = 0; j < C::LPW; j += 2) {
+                lds_stream16_x2<false>(ks, k_off[j], k_off[j + 1], lds0 + ST + j * 1024);
+                lds_stream16_x2<false>(vs, v_off[j], v_off[j + 1], lds0 + ST + C::KTILE + j * 1024);
+            }
+        } else {   // rows past the range load a valid row (masked)
+            #pragma unroll
+            for (int j = 0; j < C::LPW; ++j) {
+                const int inst = wv * C::LPW + j, cidx = inst * 64 + lane, row = cidx / C::CPR, slot = cidx % C::CPR;
+                const int key = min(row, end - 1 - base);
+                lds_stream16(ks + key * D + (slot ^ k_swz<D>(row)) * 8, smem + ST + inst * 1024);
+                lds_stream16(vs + key * D + (slot ^ v_swz<D>(row)) * 8, smem + ST + C::KTILE + inst * 1024);
+            }
         }
     };
 
+    // the wave's tiles without a mask: the tightest of its rows' ranges
+    int mem_full = m_lim[0], lo_full = r_lo[0], hi_full = r_hi[0];
+    #pragma unroll
+    for (int i = 1; i < NB; ++i) {
+        mem_full = min(mem_full, m_lim[i]);
+        lo_full = max(lo_full, r_lo[i]);
+        hi_full = min(hi_full, r_hi[i]);
+    }
+    mem_full = -wave_max_i32(-mem_full);
+    lo_full = wave_max_i32(lo_full);
+    hi_full = -wave_max_i32(-hi_full);
+
     f32x4_v o[DB][NB];
-    float m_run[NB], l_run[NB];
+    // per row: the reference maximum (unscaled scores), minus it in log2 units, the running sum
+    float m_run[NB], nms[NB], l_run[NB];
     #pragma unroll
     for (int i = 0; i < NB; ++i) {
         m_run[i] = -INFINITY;
+        nms[i] = kNoMax;
         l_run[i] = 0.f;
         #pragma unroll
         for (int db = 0; db < DB; ++db) o[db][i] = f32x4_v{0.f, 0.f, 0.f, 0.f};
     }
+    const float cs = a.scale_log2;
 
-    auto compute = [&](int t, int stage) {
-        const unsigned char *sk = smem + stage * C::STAGE, *sv = sk + C::KTILE;
+    // LDS offsets of this lane's operand reads within a stage (the half of the tile and the second
+    // row of a V pair are instruction offsets)
+    int k_at[2][KST], v_at[DB];
+    #pragma unroll
+    for (int blk = 0; blk < 2; ++blk) {
+        const int kr = 8 * (lr >> 2) + 4 * blk + (lr & 3);
+        #pragma unroll
+        for (int ks = 0; ks < KST; ++ks) k_at[blk][ks] = kr * C::RB + (((4 * ks + lg) ^ k_swz<D>(kr)) << 4);
+    }
+    #pragma unroll
+    for (int db = 0; db < DB; ++db) {
+        const int r0 = 8 * lg + (lr >> 2), byte = db * 32 + 8 * (lr & 3);
+        v_at[db] = C::KTILE + r0 * C::RB + (((byte >> 4) ^ v_swz<D>(r0)) << 4) + (byte & 8);
+    }
+
+    auto compute = [&](int t, auto stage_const) {
+        const unsigned char *st = smem + decltype(stage_const)::value * C::STAGE;
         bool is_mem;
         int end;
         const int base = tile_base(t, is_mem, end);
-        // S^T = K Q^T for the tile's keys: half h holds keys 32h .. 32h+31;
-        // A row m of block blk of pair h is key 32h + 8(m/4) + 4 blk + m%4, so
-        // accumulator element e&3 of block e>>2 in lane group lg is key 32h + 8 lg + e
-        f32x4_v sacc[C::KH][2][NB];
+        const bool full = is_mem ? base + C::KT <= mem_full : base >= lo_full && base + C::KT <= min(hi_full, end);
         #pragma unroll
-        for (int h = 0; h < C::KH; ++h)
+        for (int h = 0; h < C::KH; ++h) {
+            // S^T = K Q^T for keys 32h .. 32h+31 of the tile: A row m of block blk is key
+            // 32h + 8(m/4) + 4 blk + m%4, so accumulator element e&3 of block e>>2 in lane
+            // group lg is key 32h + 8 lg + e
+            f32x4_v sacc[2][NB];
             #pragma unroll
             for (int blk = 0; blk < 2; ++blk) {
-                const int kr = 32 * h + 8 * (lr >> 2) + 4 * blk + (lr & 3);
                 bf16x8_v kf[KST];
                 #pragma unroll
                 for (int ks = 0; ks < KST; ++ks)
-                    kf[ks] = *reinterpret_cast<const bf16x8_v *>(sk + kr * C::RB + (((4 * ks + lg) ^ k_swz(kr)) << 4));
+                    kf[ks] = *reinterpret_cast<const bf16x8_v *>(st + k_at[blk][ks] + h * 32 * C::RB);
                 #pragma unroll
                 for (int i = 0; i < NB; ++i) {
-                    sacc[h][blk][i] = f32x4_v{0.f, 0.f, 0.f, 0.f};
+                    sacc[blk][i] = f32x4_v{0.f, 0.f, 0.f, 0.f};
                     #pragma unroll
                     for (int ks = 0; ks < KST; ++ks)
-                        sacc[h][blk][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks], qf[i][ks], sacc[h][blk][i], 0, 0, 0);
+                        sacc[blk][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks], qf[i][ks], sacc[blk][i], 0, 0, 0);
                 }
             }
-        // online softmax per row block; probabilities become the B operand of PV.
-        // The running max is kept on unscaled scores (the scale is positive);
-        // p = 2^(s c - m c) is one fma into the exponential.  A tile inside
-        // every row's visible range of this wave skips the masks.
-        bf16x8_v pf[NB][C::KH];
-        const float cs = a.scale_log2;
-        #pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            const int lo = is_mem ? 0 : r_lo[i];
-            const int hi = min(end, is_mem ? m_lim[i] : r_hi[i]);
-            if (!__all(base >= lo && base + C::KT <= hi)) {
-                // edge tile: element e of half h is key base + 32h + 8lg + e; mask in place
-                const int k0 = base + 8 * lg, a0 = lo - k0, b0 = hi - k0;
+            if (!full) {
+                // edge tile: element e is key base + 32h + 8lg + e; mask in place
                 #pragma unroll
-                for (int h = 0; h < C::KH; ++h)
+                for (int i = 0; i < NB; ++i) {
+                    const int lo = is_mem ? 0 : r_lo[i], hi = min(end, is_mem ? m_lim[i] : r_hi[i]);
+                    const int k0 = base + 32 * h + 8 * lg, a0 = lo - k0, b0 = hi - k0;
                     #pragma unroll
                     for (int e = 0; e < 8; ++e) {
-                        const int kk = 32 * h + e;
-                        const bool ok = (kk >= a0) & (kk < b0);   // no short circuit: straight-line selects
-                        sacc[h][e >> 2][i][e & 3] = ok ? sacc[h][e >> 2][i][e & 3] : -INFINITY;
+                        const bool ok = (e >= a0) & (e < b0);   // no short circuit: straight-line selects
+                        sacc[e >> 2][i][e & 3] = ok ? sacc[e >> 2][i][e & 3] : -INFINITY;
                     }
-            }
-            float mt = -INFINITY;
-            #pragma unroll
-            for (int h = 0; h < C::KH; ++h)
-                #pragma unroll
-                for (int e = 0; e < 8; ++e) mt = fmaxf(mt, sacc[h][e >> 2][i][e & 3]);
-            mt = prefill_row_max(mt);
-            // lazy rescale: the reference maximum moves only when some row of the
-            // block gains more than kLazyLog2 (in log2 units); until then the
-            // probabilities stay below 2^kLazyLog2, and o and l share one reference
-            const bool grow = mt > m_run[i] && (m_run[i] == -INFINITY || (mt - m_run[i]) * cs > kLazyLog2);
-            if (__any(grow)) {
-                const float mn = fmaxf(m_run[i], mt);
-                const float alpha = __builtin_amdgcn_exp2f(fmaf(m_run[i], cs, mn == -INFINITY ? 0.f : -mn * cs));
-                m_run[i] = mn;
-                l_run[i] *= alpha;
-                #pragma unroll
-                for (int db = 0; db < DB; ++db) o[db][i] *= alpha;
-            }
-            const float ms = m_run[i] == -INFINITY ? 0.f : m_run[i] * cs;
-            float ps = 0.f;
-            #pragma unroll
-            for (int h = 0; h < C::KH; ++h) {
-                uint32_t pk[4];
-                #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float p0 = __builtin_amdgcn_exp2f(fmaf(sacc[h][(2 * e) >> 2][i][(2 * e) & 3], cs, -ms));
-                    const float p1 = __builtin_amdgcn_exp2f(fmaf(sacc[h][(2 * e + 1) >> 2][i][(2 * e + 1) & 3], cs, -ms));
-                    ps += p0 + p1;
-                    pk[e] = cvt_pk_bf16(p0, p1);
                 }
-                pf[i][h] = __builtin_bit_cast(bf16x8_v, u32x4_v{pk[0], pk[1], pk[2], pk[3]});
             }
-            l_run[i] += ps;
-        }
-        // O^T += V^T P^T: A = V^T rows (features db*16 + lr), keys 32h + 8 lg .. +7,
-        // from the transposing reads of key rows 32h + 8 lg + {0..3} and {4..7}
-        const int tr_row = 8 * lg + (lr >> 2), tr_byte = 8 * (lr & 3);
-        #pragma unroll
-        for (int h = 0; h < C::KH; ++h)
+            // Probabilities against the reference maximum as it stands, p = 2^(s c - m c): one fma into the
+            // exponential, and no maximum is taken.  A lane's sum above kLazySum (or a NaN) says that
+            // some row has outgrown its reference: only then the maxima move, o and l are rescaled and the
+            // probabilities taken again.  Rows that saw no key yet have a reference that any score outgrows.
+            float ps[NB];
+            uint32_t pk[NB][4];
+            auto probabilities = [&](int i) {
+                float p[8];
+                #pragma unroll
+                for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(fmaf(sacc[e >> 2][i][e & 3], cs, nms[i]));
+                ps[i] = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+                #pragma unroll
+                for (int e = 0; e < 4; ++e) pk[i][e] = cvt_pk_bf16(p[2 * e], p[2 * e + 1]);
+            };
+            bool grown = false;
+            #pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                probabilities(i);
+                grown |= !(ps[i] <= kLazySum);
+            }
+            if (__any(grown)) {
+                #pragma unroll
+                for (int i = 0; i < NB; ++i) {
+                    float mt = -INFINITY;
+                    #pragma unroll
+                    for (int e = 0; e < 8; ++e) mt = fmaxf(mt, sacc[e >> 2][i][e & 3]);
+                    const float mn = fmaxf(m_run[i], prefill_row_max(mt));
+                    const float alpha = mn == m_run[i] ? 1.f : __builtin_amdgcn_exp2f((m_run[i] - mn) * cs);
+                    m_run[i] = mn;
+                    nms[i] = mn == -INFINITY ? kNoMax : -mn * cs;
+                    l_run[i] *= alpha;
+                    #pragma unroll
+                    for (int db = 0; db < DB; ++db) o[db][i] *= alpha;
+                    probabilities(i);
+                }
+            }
+            bf16x8_v pf[NB];
+            #pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                l_run[i] += ps[i];
+                pf[i] = __builtin_bit_cast(bf16x8_v, u32x4_v{pk[i][0], pk[i][1], pk[i][2], pk[i][3]});
+            }
+            // O^T += V^T P^T: A = V^T rows (features db*16 + lr), keys 32h + 8 lg .. +7,
+            // from the transposing reads of key rows 32h + 8 lg + {0..3} and {4..7}
             #pragma unroll
             for (int db = 0; db < DB; ++db) {
-                const int byte = db * 32 + tr_byte, chunk = byte >> 4, half = byte & 8;
-                const int r0 = 32 * h + tr_row, r1 = r0 + 4;
-                const v4s_t lo = lds_read_tr16(sv + r0 * C::RB + ((chunk ^ v_swz(r0)) << 4) + half);
-                const v4s_t hi = lds_read_tr16(sv + r1 * C::RB + ((chunk ^ v_swz(r1)) << 4) + half);
+                const v4s_t lo = lds_read_tr16(st + v_at[db] + h * 32 * C::RB);
+                const v4s_t hi = lds_read_tr16(st + v_at[db] + (h * 32 + 4) * C::RB);
                 const bf16x8_v vf = __builtin_bit_cast(bf16x8_v, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
                 #pragma unroll
-                for (int i = 0; i < NB; ++i) o[db][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[i][h], o[db][i], 0, 0, 0);
+                for (int i = 0; i < NB; ++i) o[db][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[i], o[db][i], 0, 0, 0);
             }
+        }
     };
 
-    store_lds(0, load_regs(0));
+    // The loads of tile t + 1 go out before tile t is used and have landed by its end (the waits are
+    // explicit: the compiler does not count direct loads).  Two tiles a round, so that every LDS
+    // address has its stage as a constant.
+    load_tile(0, std::integral_constant<int, 0>());
+    wait_vm(0);
     __syncthreads();
-    // Unconditional: the last pass reloads and restages its own tile into the
-    // idle stage (nothing reads it), so the staging registers stay registers
-    // (a conditional fill and drain sent them to scratch memory).
-    for (int t = 0; t < nt; ++t) {
-        const StageRegs next = load_regs(t + 1 < nt ? t + 1 : t);
-        compute(t, t & 1);
-        store_lds((t + 1) & 1, next);
+    for (int t = 0; t < nt; t += 2) {
+        if (t + 1 < nt) load_tile(t + 1, std::integral_constant<int, 1>());
+        compute(t, std::integral_constant<int, 0>());
+        if (t + 1 >= nt) break;
+        wait_vm(0);
+        __syncthreads();
+        if (t + 2 < nt) load_tile(t + 2, std::integral_constant<int, 0>());
+        compute(t + 1, std::integral_constant<int, 1>());
+        wait_vm(0);
         __syncthreads();
     }
 

@@ -34,8 +34,8 @@
 // CU.  Wave w < KS*NB owns 16-row block w % NB and key group w / NB of every
 // slab; consecutive waves -- on different SIMDs -- take different row blocks,
 // and one wave's exponentials overlap another's matrix products.  K rows land
-// with their 16-byte chunks XOR-swizzled by row, V rows by 2 (row mod 4), V^T
-// rows by feature, so every operand read is conflict-free.  The ring runs on
+// with their 16-byte chunks XOR-swizzled by row (k_swz, v_swz), V^T rows by
+// feature, so every operand read is conflict-free.  The ring runs on
 // across units: the next unit's slabs and its query rows (direct loads into a
 // small LDS area, older than the unit's first slab) are in flight while the
 // current unit finishes.
@@ -80,12 +80,6 @@ struct StreamCfg {
     static_assert(SMEM + 64 <= 160 * 1024, "LDS");
 };
 
-__device__ __forceinline__ int vk_swz(int k) { return (k & 3) | (((k >> 3) & 1) << 2); }
-// natural V rows: 16-byte chunk c of key row k sits at chunk c ^ vn_swz(k); a
-// transposing read of 16 lanes covers rows k0 .. k0+3 (k0 a multiple of 4) x
-// two adjacent chunks, and XOR with 2 (k mod 4) puts the eight (row, chunk)
-// pairs on distinct banks
-__device__ __forceinline__ int vn_swz(int k) { return (k & 3) << 1; }
 typedef short v4s_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ v4s_t lds_read_tr16(const unsigned char *p) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s_t *)(p));
@@ -327,10 +321,10 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
     #pragma unroll
     for (int j = 0; j < LPW; ++j) {
         const int cidx = (wave * LPW + j) * 64 + lane, kr = cidx / C::CPR, slot = cidx % C::CPR;
-        k_off[j] = kr * C::RB + ((slot ^ vk_swz(kr)) << 4) - 1024 * j;
-        v_off[j] = kr * C::RB + ((slot ^ vn_swz(kr)) << 4) - 1024 * j;
+        k_off[j] = kr * C::RB + ((slot ^ k_swz<D>(kr)) << 4) - 1024 * j;
+        v_off[j] = kr * C::RB + ((slot ^ v_swz<D>(kr)) << 4) - 1024 * j;
     }
-    static_assert(LPW == 2, "lds_stream16_nt_x2");
+    static_assert(LPW == 2, "lds_stream16_x2");
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(smem)) + wv * LPW * 1024;
     // the first slab of a unit (or of the run) needs a free query area
     auto can_issue = [&]() {
@@ -363,8 +357,8 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
             }
         }
         if (one) {
-            lds_stream16_nt_x2(k0, k_off[0], k_off[1], lds0 + i_stage);
-            lds_stream16_nt_x2(v0, v_off[0], v_off[1], lds0 + i_stage + C::KBYTES);
+            lds_stream16_x2<true>(k0, k_off[0], k_off[1], lds0 + i_stage);
+            lds_stream16_x2<true>(v0, v_off[0], v_off[1], lds0 + i_stage + C::KBYTES);
         } else if constexpr (DRAFT) {
             // row by row: memory, ring, the new token; rows past the end repeat the last one (masked),
             // those of an empty row read the queries (never used)
@@ -383,8 +377,8 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
                 const bf16_t *vp = i < 0 ? i_v + (int64_t)(key - i_t * C::SLAB) * D
                                  : i < i_wlen ? i_wv + (size_t)r * D : bits_ptr<const bf16_t>(ring.vn) + nrow;
                 if (n == 0) kp = vp = bits_ptr<const bf16_t>(a.q);
-                lds_stream16_nt(kp + (slot ^ vk_swz(kr)) * 8, st + inst * 1024);
-                lds_stream16_nt(vp + (slot ^ vn_swz(kr)) * 8, st + C::KBYTES + inst * 1024);
+                lds_stream16_nt(kp + (slot ^ k_swz<D>(kr)) * 8, st + inst * 1024);
+                lds_stream16_nt(vp + (slot ^ v_swz<D>(kr)) * 8, st + C::KBYTES + inst * 1024);
             }
         } else {
             unsigned char *st = smem + i_stage;
@@ -395,9 +389,9 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
                 const int cidx = inst * 64 + lane;
                 const int kr = cidx / C::CPR, slot = cidx % C::CPR;
                 const int key = min(kr, keys - 1);   // rows past len: a valid row, masked
-                lds_stream16_nt(i_k + key * D + (slot ^ vk_swz(kr)) * 8, st + inst * 1024);
+                lds_stream16_nt(i_k + key * D + (slot ^ k_swz<D>(kr)) * 8, st + inst * 1024);
                 if constexpr (VNAT) {
-                    lds_stream16_nt(i_v + key * D + (slot ^ vn_swz(kr)) * 8, st + C::KBYTES + inst * 1024);
+                    lds_stream16_nt(i_v + key * D + (slot ^ v_swz<D>(kr)) * 8, st + C::KBYTES + inst * 1024);
                 } else {
                     // V^T: feature cidx / VCH, LDS slot holds key chunk slot ^ (f & 7)
                     const int f = cidx / C::VCH, vs = cidx % C::VCH;
@@ -457,7 +451,7 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
             const int kr = 32 * kh + 8 * (lr >> 2) + 4 * blk + (lr & 3);
             #pragma unroll
             for (int ks = 0; ks < KST; ++ks)
-                kf[blk][ks] = *reinterpret_cast<const bf16x8_v *>(st + kr * C::RB + (((4 * ks + lg) ^ vk_swz(kr)) << 4));
+                kf[blk][ks] = *reinterpret_cast<const bf16x8_v *>(st + kr * C::RB + (((4 * ks + lg) ^ k_swz<D>(kr)) << 4));
         }
         const unsigned char *sv8 = st + C::KBYTES;
         if constexpr (VNAT) {
@@ -468,8 +462,8 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
             #pragma unroll
             for (int db = 0; db < DB; ++db) {
                 const int byte = db * 32 + tr_byte, chunk = byte >> 4, half = byte & 8;
-                const v4s_t lo = lds_read_tr16(sv8 + r0 * C::RB + ((chunk ^ vn_swz(r0)) << 4) + half);
-                const v4s_t hi = lds_read_tr16(sv8 + r1 * C::RB + ((chunk ^ vn_swz(r1)) << 4) + half);
+                const v4s_t lo = lds_read_tr16(sv8 + r0 * C::RB + ((chunk ^ v_swz<D>(r0)) << 4) + half);
+                const v4s_t hi = lds_read_tr16(sv8 + r1 * C::RB + ((chunk ^ v_swz<D>(r1)) << 4) + half);
                 vf[db] = __builtin_bit_cast(bf16x8_v, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
             }
         } else {
@@ -566,7 +560,7 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
                 const int kr = len - 1 - (nt - 1) * C::SLAB, ch = tid % C::CPR;
                 const bool is_v = tid >= C::CPR;
                 const uint4 x = *reinterpret_cast<const uint4 *>(st + (is_v ? C::KBYTES : 0) + kr * C::RB +
-                                                                 ((ch ^ (is_v ? vn_swz(kr) : vk_swz(kr))) << 4));
+                                                                 ((ch ^ (is_v ? v_swz<D>(kr) : k_swz<D>(kr))) << 4));
                 int r = ring.start(b) + __builtin_amdgcn_readlane(a.rec.y, b);
                 if (r >= ring.cap) r -= ring.cap;
                 bf16_t *dst = bits_ptr<bf16_t>(is_v ? ring.wv : ring.wk) + b * ring.seq + c * ring.head + (size_t)r * D;

@@ -172,3 +172,12 @@ def test_growing_scores_rebase_the_running_maximum(d, ramp):
     # keys scaled by 1 .. 1 + ramp along the prefix: the late tiles' scores exceed the early ones' by
     # more than 2^8, so the lazily rebased maximum moves within a pass; at ramp 11 scores reach ~50
     _run(8, 2, d, S=4, W=300, r=8, u=2, P_list=[2500, 1700], seed=23, ramp=ramp)
+
+
+@pytest.mark.parametrize("d,Hq,Hkv", [(64, 8, 2), (128, 8, 2), (64, 8, 1), (128, 2, 2)])
+def test_tile_counts_and_rows_without_keys(d, Hq, Hkv):
+    # one tile, an even and an odd number of them (the loop takes two a round), a first tile wholly outside some
+    # rows' windows (W smaller than a tile and than a query block), prefixes inside the sinks, shorter than a
+    # query block and past it, r = 1 (a slot per token)
+    _run(Hq, Hkv, d, S=4, W=5, r=1, u=1, P_list=[1, 3, 5, 64, 65, 129, 200], seed=31 + d)
+    _run(Hq, Hkv, d, S=0, W=70, r=8, u=2, P_list=[63, 64, 66, 130, 321], seed=32 + d)
