@@ -1,9 +1,11 @@
 """MI355X-native hot path of memory-augmented sliding-window (MASW) drafting.
 
-Thin ctypes binding over libmad.so (C ABI in include/mad.h).  This module
-only marshals arguments -- tensor pointers, strides, host length arrays and
-the current HIP stream -- into the C entry points; every step of the path
-runs in the library's HIP kernels.  PyTorch provides device memory and
+Thin binding over libmad.so (C ABI in include/mad.h).  This module only
+marshals arguments -- tensor pointers, strides, host length arrays and the
+current HIP stream -- into the C entry points; every step of the path runs in
+the library's HIP kernels.  The ordinary call (plain tensors, outputs given,
+lengths in lists) is marshalled by _fastcall.so in native code; whatever that
+does not handle, failed checks among it, takes the ctypes path below.  PyTorch provides device memory and
 streams.  The library is loaded on first use; if libmad.so is missing that
 first call raises: there is no fallback.
 
@@ -43,7 +45,7 @@ _LIB = None
 
 
 def _load_library():
-    global _LIB
+    global _LIB, _FAST
     if _LIB is not None:
         return _LIB
     if not os.path.exists(LIB_PATH):
@@ -80,8 +82,31 @@ def _load_library():
                "mad_rmsnorm_qkv_rope", "mad_linear_residual", "mad_rmsnorm_swiglu", "mad_probe_stream_read",
                "mad_probe_shared_read", "mad_probe_empty", "mad_probe_handoff_latency"):
         getattr(lib, fn).restype = ctypes.c_int
-    _LIB = lib
+    _LIB, _FAST = lib, None
     return lib
+
+
+_FAST = None
+_FAST_ENTRIES = ("mad_draft_decode_attn", "mad_draft_step_attn", "mad_memory_update", "mad_verify_attn",
+                 "mad_verify_attn_vt", "mad_accept_greedy", "mad_accept_stochastic", "mad_rmsnorm_qkv_rope",
+                 "mad_linear_residual", "mad_rmsnorm_swiglu", "mad_workspace_bytes")
+
+
+def _fast():
+    """The native marshalling module, bound to the loaded library.  Its functions return the C entry
+    point's code, or None (nothing enqueued) for a call that the ctypes path has to take."""
+    global _FAST
+    lib = _load_library()
+    if _FAST is None:
+        try:
+            from . import _fastcall
+        except ImportError as e:
+            raise ImportError("_fastcall.so is missing or does not load: build it with "
+                              "`python -m paper_2608_30252_amd.build`") from e
+        _fastcall.bind(tuple(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _FAST_ENTRIES), KV,
+                       _default_ws, torch._C._cuda_getCurrentRawStream)
+        _FAST = _fastcall
+    return _FAST
 
 
 class MadError(RuntimeError):
@@ -251,6 +276,11 @@ def draft_decode_attn(q: torch.Tensor, mem: Optional[KV], win: Optional[KV],
     Attends over mem rows [0, len) then the window ring rows start..start+len-1
     (mod cap) then the new token (k_new/v_new [B, Hkv, d], which is also
     written into the ring at row (start + len) % cap)."""
+    if out is not None and lse is not None:
+        rc = (_FAST or _fast()).attn(q, mem, win, k_new, v_new, out, lse, scale, ws, None)
+        if rc is not None:
+            _check(rc)
+            return out, lse
     B, Hq, Hkv, d, out, lse, scale, mv, wv = _decode_args(q, mem, win, k_new, v_new, out, lse, scale)
     nbytes = workspace_bytes(MAD_OP_DECODE, B, Hq, Hkv, d)
     w = _ws_for(q.device, nbytes, ws)
@@ -287,6 +317,11 @@ def draft_step_attn(q: torch.Tensor, mem: Optional[KV], win: Optional[KV], k_new
     """draft_decode_attn with a per-row new-token mode (host list of B values):
     0 = no new token, 1 = attend k_new/v_new[b] only, 2 = attend and append it
     to the row's ring.  Rows may alias one sequence's buffers (batch dim 1)."""
+    if out is not None and lse is not None and new_mode is not None:
+        rc = (_FAST or _fast()).attn(q, mem, win, k_new, v_new, out, lse, scale, ws, new_mode)
+        if rc is not None:
+            _check(rc)
+            return out, lse
     B, Hq, Hkv, d, out, lse, scale, mv, wv = _decode_args(q, mem, win, k_new, v_new, out, lse, scale)
     _need(len(new_mode) == B, "new_mode needs one entry per row")
     modes = (ctypes.c_uint8 * B)(*[int(m) for m in new_mode])
@@ -306,6 +341,10 @@ def memory_update(x: torch.Tensor, w_kv: torch.Tensor, pos, mem: KV, fire=None, 
 
     Appends the slots' K (rotated at pos) and V at mem rows len[b]..len[b]+n_new-1
     of every firing sequence.  The caller then raises its lengths."""
+    rc = (_FAST or _fast()).update(x, w_kv, pos, mem, fire, rope_base)
+    if rc is not None:
+        _check(rc)
+        return
     _need(x.dim() == 3, "x must be [B, n_new, D]")
     B, n_new, D = x.shape
     Hkv, d = mem.k.shape[1], mem.k.shape[3]
@@ -345,6 +384,11 @@ def verify_attn(q: torch.Tensor, kv: KV, out=None, lse=None, scale: Optional[flo
     """q [B, T, Hq, d]; kv: the verifier's cache as it is, K and V [B, Hkv, cap, d]
     (rows of d), kv.length[b] rows valid with the T new tokens at len-T..len-1.
     Returns (out [B, T, Hq, d], lse [B, T, Hq])."""
+    if out is not None and lse is not None:
+        rc = (_FAST or _fast()).verify(q, kv, out, lse, scale, ws)
+        if rc is not None:
+            _check(rc)
+            return out, lse
     B, T, Hq, d = q.shape
     Hkv = kv.k.shape[1]
     _need(kv.start is None, "the verifier's cache is linear (no ring start)")
@@ -363,6 +407,11 @@ def verify_attn_vt(q: torch.Tensor, k: torch.Tensor, vt: torch.Tensor, length, o
     """q [B, T, Hq, d]; k [B, Hkv, cap, d]; vt [B, Hkv, d, cap] (values stored
     key-contiguous per feature); the T new tokens sit at rows len-T..len-1.
     Returns (out [B, T, Hq, d], lse [B, T, Hq])."""
+    if out is not None and lse is not None:
+        rc = (_FAST or _fast()).verify_vt(q, k, vt, length, out, lse, scale, ws)
+        if rc is not None:
+            _check(rc)
+            return out, lse
     B, T, Hq, d = q.shape
     Hkv, cap = k.shape[1], k.shape[2]
     if vt.shape != (B, Hkv, d, cap) or k.shape != (B, Hkv, cap, d):
@@ -389,6 +438,11 @@ def accept_greedy(logits: torch.Tensor, draft_tok: Optional[torch.Tensor], n_acc
                   ws: Optional[torch.Tensor] = None):
     """logits [B, T, V] (fp32 or bf16), draft_tok int32 [B, T-1] on the device.
     Returns (n_accept int32 [B], next_tok int32 [B]) on the device."""
+    if n_accept is not None and next_tok is not None:
+        rc = (_FAST or _fast()).greedy(logits, draft_tok, n_accept, next_tok, ws)
+        if rc is not None:
+            _check(rc)
+            return n_accept, next_tok
     B, T, V = logits.shape
     dev = logits.device
     if n_accept is None:
@@ -414,6 +468,11 @@ def accept_stochastic(p: torch.Tensor, q: Optional[torch.Tensor], draft_tok: Opt
     """p [B, T, V] float32 target probabilities, q [B, T-1, V] float32 draft
     probabilities, draft_tok int32 [B, T-1], u float32 [B, T] uniforms, all on
     the device.  Returns (n_accept int32 [B], next_tok int32 [B])."""
+    if n_accept is not None and next_tok is not None:
+        rc = (_FAST or _fast()).stoch(p, q, draft_tok, u, n_accept, next_tok, ws)
+        if rc is not None:
+            _check(rc)
+            return n_accept, next_tok
     B, T, V = p.shape
     dev = p.device
     if n_accept is None:
@@ -492,6 +551,11 @@ def rmsnorm_qkv_rope(x: torch.Tensor, gamma: torch.Tensor, w_qkv: torch.Tensor, 
                      rope_base: float = 500000.0, kv_from_row0: bool = False):
     """x [R, D] -> q [R, Hq, d], k and v [R, Hkv, d] (q, k rotated at pos), and the
     normalised rows xn [R, D] when given."""
+    if q is not None and k is not None and v is not None:
+        rc = (_FAST or _fast()).qkv(x, gamma, w_qkv, pos, Hq, Hkv, d, q, k, v, xn, eps, rope_base, kv_from_row0)
+        if rc is not None:
+            _check(rc)
+            return q, k, v
     R, D = x.shape
     if q is None:
         q = torch.empty((R, Hq, d), dtype=x.dtype, device=x.device)
@@ -515,6 +579,11 @@ def rmsnorm_qkv_rope(x: torch.Tensor, gamma: torch.Tensor, w_qkv: torch.Tensor, 
 
 def linear_residual(x: torch.Tensor, w: torch.Tensor, res: torch.Tensor, out: Optional[torch.Tensor] = None):
     """out [R, N] = res + x W^T."""
+    if out is not None:
+        rc = (_FAST or _fast()).linear(x, w, res, out)
+        if rc is not None:
+            _check(rc)
+            return out
     R, D = x.shape
     N = w.shape[0]
     if out is None:
@@ -530,6 +599,11 @@ def linear_residual(x: torch.Tensor, w: torch.Tensor, res: torch.Tensor, out: Op
 def rmsnorm_swiglu(x: torch.Tensor, gamma: torch.Tensor, w_gate_up: torch.Tensor,
                    out: Optional[torch.Tensor] = None, eps: float = 1e-5):
     """out [R, F] = silu(xn W_gate^T) * (xn W_up^T), xn = rmsnorm(x) * gamma."""
+    if out is not None:
+        rc = (_FAST or _fast()).swiglu(x, gamma, w_gate_up, out, eps)
+        if rc is not None:
+            _check(rc)
+            return out
     R, D = x.shape
     Fd = w_gate_up.shape[0] // 2
     if out is None:

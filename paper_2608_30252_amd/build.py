@@ -1,4 +1,4 @@
-"""Build libmad.so (HIP, gfx950) in-tree.
+"""Build libmad.so (HIP, gfx950) and the Python binding's _fastcall.so in-tree.
 
     python -m paper_2608_30252_amd.build            # the library
     python -m paper_2608_30252_amd.build --trace    # + libmad_trace.so, the diagnostic phase-trace build
@@ -16,6 +16,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmad.so")
+FASTCALL = os.path.join(HERE, "_fastcall.so")
 BUILD_DIR = os.path.join(HERE, "_build")
 # the same sources with the kernels' phase marks compiled in (MAD_PHASE_TRACE):
 # read by paper_2608_30252_amd/phase_trace.py, never by the product path
@@ -68,6 +69,32 @@ def build(verbose: bool = False, out: str = LIB, build_dir: str = BUILD_DIR, def
     return out
 
 
+def build_fastcall(verbose: bool = False) -> str:
+    """csrc/fastcall.cpp against the installed torch's headers and libraries (the ones its import loads)."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    tmp = FASTCALL + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(HERE, "..", "include"), "-I", sysconfig.get_paths()["include"]]
+    for p in include_paths():
+        cmd += ["-isystem", p]
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd += [os.path.join(CSRC, "fastcall.cpp"), "-o", tmp, "-L", libs, f"-Wl,-rpath,{libs}", "-ltorch_python",
+            "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on fastcall.cpp:\n{r.stderr}")
+    if r.stderr.strip() and verbose:
+        print(r.stderr, flush=True)
+    os.replace(tmp, FASTCALL)
+    return FASTCALL
+
+
 def build_trace(verbose: bool = False) -> str:
     return build(verbose, out=TRACE_LIB, build_dir=TRACE_BUILD_DIR, defines=("MAD_PHASE_TRACE",))
 
@@ -75,6 +102,7 @@ def build_trace(verbose: bool = False) -> str:
 if __name__ == "__main__":
     build(verbose="-v" in sys.argv)
     print(LIB)
+    print(build_fastcall(verbose="-v" in sys.argv))
     if "--trace" in sys.argv:
         build_trace(verbose="-v" in sys.argv)
         print(TRACE_LIB)

@@ -1,0 +1,67 @@
+"""The native marshalling of the binding against the ctypes path.
+
+A call whose lengths and positions come as numpy arrays is not the ordinary one
+and takes the ctypes path; the same values in lists take the native one.  Both
+must pass the same arguments on, so every output is bit-identical; and a failed
+check or a return code of the library raises the same error on both.
+"""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _calls(mad, as_seq):
+    """name -> (output tensors, call) over the entry points with both paths; `as_seq` makes the host sequences."""
+    from paper_2608_30252_amd import synth
+    dev = "cuda"
+    n = lambda shape, seed, std=1.0, dt=torch.bfloat16: synth.normal(shape, seed, std=std, dtype=dt).to(dev)
+    B, Hq, Hkv, d, D, T = 3, 8, 2, 64, 2048, 3
+    q, mk, mv = n((B, Hq, d), 1), n((B, Hkv, 40, d), 2), n((B, Hkv, 40, d), 3)
+    wk, wv, kn, vn = n((B, Hkv, 50, d), 4), n((B, Hkv, 50, d), 5), n((B, Hkv, d), 6), n((B, Hkv, d), 7)
+    mem, win = mad.KV(mk, mv, as_seq([7, 0, 31])), mad.KV(wk, wv, as_seq([20, 49, 3]), as_seq([45, 1, 9]))
+    o, l = torch.empty_like(q), torch.empty(B, Hq, device=dev)
+    yield "decode", [o, l, wk, wv], lambda: mad.draft_decode_attn(q, mem, win, kn, vn, o, l)
+    o2, l2 = torch.empty_like(q), torch.empty(B, Hq, device=dev)
+    yield "step", [o2, l2, wk, wv], lambda: mad.draft_step_attn(q, mem, win, kn, vn, as_seq([1, 2, 0]), o2, l2, 0.2)
+    x, w = n((B, 2, D), 8), n((2 * Hkv * d, D), 9, 0.02)
+    yield "update", [mk, mv], lambda: mad.memory_update(x, w, [as_seq([3 * b, 9]) for b in range(B)],
+                                                        mad.KV(mk, mv, as_seq([7, 0, 31])), fire=as_seq([1, 0, 1]))
+    qv, vk, vv = n((B, T, Hq, d), 10), n((B, Hkv, 64, d), 11), n((B, Hkv, 64, d), 12)
+    ov, lv = torch.empty_like(qv), torch.empty(B, T, Hq, device=dev)
+    yield "verify", [ov, lv], lambda: mad.verify_attn(qv, mad.KV(vk, vv, as_seq([3, 64, 40])), ov, lv)
+    vt = vv.transpose(2, 3).contiguous()
+    ot, lt = torch.empty_like(qv), torch.empty(B, T, Hq, device=dev)
+    yield "verify_vt", [ot, lt], lambda: mad.verify_attn_vt(qv, vk, vt, as_seq([3, 64, 40]), ot, lt)
+    xr, gm, wq = n((2, D), 13), n((D,), 14), n(((Hq + 2 * Hkv) * d, D), 15, 0.02)
+    qo, ko, vo, xn = (torch.empty(s, dtype=torch.bfloat16, device=dev) for s in ((2, Hq, d), (2, Hkv, d), (2, Hkv, d), (2, D)))
+    yield "qkv", [qo, ko, vo, xn], lambda: mad.rmsnorm_qkv_rope(xr, gm, wq, as_seq([5, 70]), Hq, Hkv, d, qo, ko, vo, xn)
+
+
+def test_native_and_ctypes_marshalling_agree():
+    import paper_2608_30252_amd as mad
+    for (name, a, f), (_, b, g) in zip(_calls(mad, list), _calls(mad, np.array)):
+        for call in (f, g, f, g):   # the first native call finds no workspace yet and leaves it to the ctypes path
+            call()
+        torch.cuda.synchronize()
+        for i, (s, t) in enumerate(zip(a, b)):
+            bits = torch.int16 if s.dtype == torch.bfloat16 else torch.int32
+            assert torch.equal(s.view(bits), t.view(bits)), f"{name}: output {i}"
+
+
+@pytest.mark.parametrize("as_seq", [list, np.array])
+def test_errors_are_the_same_on_both_paths(as_seq):
+    import paper_2608_30252_amd as mad
+    q = torch.zeros(2, 8, 64, dtype=torch.bfloat16, device="cuda")
+    k = torch.zeros(2, 2, 16, 64, dtype=torch.bfloat16, device="cuda")
+    o, l = torch.empty_like(q), torch.empty(2, 8, device="cuda")
+    with pytest.raises(mad.MadError, match="exceeds cap") as e:
+        mad.draft_decode_attn(q, mad.KV(k, k, as_seq([17, 1])), None, None, None, o, l)
+    assert e.value.code == mad.MAD_EINVAL
+    with pytest.raises(ValueError, match="head_dim"):
+        mad.draft_decode_attn(q, mad.KV(k[..., :32].contiguous(), k[..., :32].contiguous(), as_seq([1, 1])), None, None,
+                              None, o, l)
+    with pytest.raises(ValueError, match="contiguous"):
+        mad.draft_decode_attn(q.transpose(0, 1).contiguous().transpose(0, 1), mad.KV(k, k, as_seq([1, 1])), None, None,
+                              None, o, l)
