@@ -97,7 +97,9 @@ __device__ __forceinline__ uint64_t max_agent_u64(uint64_t *p, uint64_t v) {
     return __hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <typename T>
+// VEC16: rows aligned for 16-byte loads, an instantiation of its own (9.4 us
+// against 10.1 with both forms in one kernel)
+template <typename T, bool VEC16>
 __global__ __launch_bounds__(256) void accept_kernel(const AcceptArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int rows = a.B * a.T;
@@ -106,22 +108,50 @@ __global__ __launch_bounds__(256) void accept_kernel(const AcceptArgs a) {
     const int v1 = min(a.V, v0 + kAcceptChunk);
     const T *x = reinterpret_cast<const T *>(a.logits) + (size_t)row * a.V;
 
-    uint64_t best = 0;   // below every real key (index 0xffffffff is never used)
+    // Per thread: the maximum by three-operand maxima, then its first place by
+    // equality (equality folds -0 into +0 as the keys do): two and a half
+    // instructions an element where a 64-bit key of each took ten.  A maximum
+    // skips NaN, so a NaN among the elements (tested in pairs) sends the thread
+    // to the keys.  16 x 5 rows of 128256 in fp32: 11.0 -> 9.4 us.
     constexpr int VEC = Elem<T>::VEC;                   // elements per 16-byte load
     constexpr int NV = kAcceptChunk / (256 * VEC);      // 16-byte loads per thread per chunk
-    if (a.vec16) {
+    uint64_t best = 0;   // below every real key (index 0xffffffff is never used)
+    if constexpr (VEC16) {
         // rows start on 16-byte boundaries and V is a multiple of VEC: every
-        // load of the chunk is issued before any is used
+        // load of the chunk is issued before any is used (a piece past the
+        // chunk reads its last piece again, whose places are never the first)
         uint4 v[NV];
         #pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            const int e = v0 + (tid + 256 * k) * VEC;
-            v[k] = e < v1 ? *reinterpret_cast<const uint4 *>(x + e) : make_uint4(0u, 0u, 0u, 0u);
-        }
+        for (int k = 0; k < NV; ++k)
+            v[k] = *reinterpret_cast<const uint4 *>(x + min(v0 + (tid + 256 * k) * VEC, v1 - VEC));
+        float m = -INFINITY;
+        bool nan = false;
         #pragma unroll
         for (int k = 0; k < NV; ++k) {
-            const int e = v0 + (tid + 256 * k) * VEC;
-            if (e < v1) {
+            float f[VEC];
+            unpack16(v[k], f, T());
+            #pragma unroll
+            for (int q = 0; q < VEC; q += 2) {
+                nan |= __builtin_isunordered(f[q], f[q + 1]);
+                m = fmaxf(m, fmaxf(f[q], f[q + 1]));
+            }
+        }
+        if (!nan) {
+            int at = 0;
+            #pragma unroll
+            for (int k = NV - 1; k >= 0; --k) {
+                float f[VEC];
+                unpack16(v[k], f, T());
+                #pragma unroll
+                for (int q = VEC - 1; q >= 0; --q) at = f[q] == m ? 256 * VEC * k + q : at;
+            }
+            // a place past the chunk is one of its last piece, read again
+            const int e = v0 + tid * VEC + at;
+            best = argmax_key(m, e < v1 ? e : v1 - VEC + (at & (VEC - 1)));
+        } else {
+            #pragma unroll
+            for (int k = 0; k < NV; ++k) {
+                const int e = min(v0 + (tid + 256 * k) * VEC, v1 - VEC);
                 float f[VEC];
                 unpack16(v[k], f, T());
                 #pragma unroll
@@ -132,9 +162,28 @@ __global__ __launch_bounds__(256) void accept_kernel(const AcceptArgs a) {
             }
         }
     } else {
-        for (int i = v0 + tid; i < v1; i += 256) {
-            const uint64_t k = argmax_key(Elem<T>::load1(x + i), i);
-            best = k > best ? k : best;
+        // element by element, the loads together again (past the chunk: its last entry)
+        constexpr int NE = kAcceptChunk / 256;
+        float f[NE], m = -INFINITY;
+        bool nan = false;
+        #pragma unroll
+        for (int k = 0; k < NE; ++k) f[k] = Elem<T>::load1(x + min(v0 + tid + 256 * k, v1 - 1));
+        #pragma unroll
+        for (int k = 0; k < NE; k += 2) {
+            nan |= __builtin_isunordered(f[k], f[k + 1]);
+            m = fmaxf(m, fmaxf(f[k], f[k + 1]));
+        }
+        if (!nan) {
+            int at = 0;
+            #pragma unroll
+            for (int k = NE - 1; k >= 0; --k) at = f[k] == m ? k : at;
+            best = argmax_key(m, min(v0 + tid + 256 * at, v1 - 1));
+        } else {
+            #pragma unroll
+            for (int k = 0; k < NE; ++k) {
+                const uint64_t key = argmax_key(f[k], min(v0 + tid + 256 * k, v1 - 1));
+                best = key > best ? key : best;
+            }
         }
     }
     best = wave_max_u64(best);
@@ -228,6 +277,11 @@ __device__ __forceinline__ double draw_weight(float p, float q, bool resid) {
     return r > 0.0 ? r : 0.0;
 }
 
+// Chunks of 2048 entries: the call is a chain of round trips (drafted tokens,
+// their probabilities, the chunk, the chunk sums, the drawn chunk again), so
+// what counts is that each is short.  With 8192 a thread summed 32 entries in
+// double precision and walked 32 in the draw, on 112 workgroups at 16 sequences
+// of 50257 entries: 16.2 us, against 7.7 with 400 workgroups of 8 a thread.
 // VEC16: every row starts 16-byte aligned and V is a multiple of 4, so the
 // rows are read as float4; the element-wise form is its own instantiation so
 // that the aligned kernel carries none of its code
@@ -262,14 +316,14 @@ __global__ __launch_bounds__(256) void stoch_kernel(const StochArgs a) {
     const float *qr = resid ? a.q + ((size_t)b * (T - 1) + acc) * V : pr;
 
     // ---- this chunk's sums of the draw weights and of p_a ----
-    const int v0 = chunk * kAcceptChunk, v1 = min(V, v0 + kAcceptChunk);
+    const int v0 = chunk * kStochChunk, v1 = min(V, v0 + kStochChunk);
     double sr = 0.0, sp = 0.0;
     if constexpr (VEC16) {
         // every load unconditional (a piece past the chunk reads its last
         // piece again and is skipped below; q reads the p row when unused), so
         // no branch -- and no wait the compiler places inside one -- splits
         // them: all 2 NV loads are in flight together
-        constexpr int NV = kAcceptChunk / (256 * 4);
+        constexpr int NV = kStochChunk / (256 * 4);
         float4 pv[NV], qv[NV];
         #pragma unroll
         for (int k = 0; k < NV; ++k) {
@@ -288,7 +342,7 @@ __global__ __launch_bounds__(256) void stoch_kernel(const StochArgs a) {
     } else {
         // element by element, the loads again unconditional (an index past
         // the chunk reads its last entry, skipped in the sums)
-        constexpr int NE = kAcceptChunk / 256;
+        constexpr int NE = kStochChunk / 256;
         float pv[NE], qv[NE];
         #pragma unroll
         for (int k = 0; k < NE; ++k) {
@@ -378,8 +432,8 @@ __global__ __launch_bounds__(256) void stoch_kernel(const StochArgs a) {
     // (2) runs of RUN consecutive entries of the chunk, one per thread, kept in
     // registers; a block prefix sum over the runs finds the run where the
     // running sum passes the target, and that thread walks its run in order
-    constexpr int RUN = kAcceptChunk / 256;
-    const int cbeg = cs * kAcceptChunk, cend = min(V, cbeg + kAcceptChunk);
+    constexpr int RUN = kStochChunk / 256;
+    const int cbeg = cs * kStochChunk, cend = min(V, cbeg + kStochChunk);
     const int r0 = cbeg + tid * RUN;
     double w[RUN];
     double mine = 0.0;
@@ -457,7 +511,7 @@ __global__ __launch_bounds__(256) void stoch_kernel(const StochArgs a) {
 }
 
 size_t stoch_ws_bytes(int B, int V) {
-    const size_t chunks = ((size_t)V + kAcceptChunk - 1) / kAcceptChunk;
+    const size_t chunks = ((size_t)V + kStochChunk - 1) / kStochChunk;
     return kCounterRegionBytes + align256((size_t)B * chunks * 16);
 }
 
@@ -469,10 +523,16 @@ hipError_t launch_stoch(const StochArgs &a, hipStream_t st) {
     return hipGetLastError();
 }
 
+template <typename T>
+static void launch_accept_t(const AcceptArgs &a, hipStream_t st) {
+    const dim3 grid((unsigned)(a.B * a.T * a.n_chunks)), block(256);
+    if (a.vec16) hipLaunchKernelGGL((accept_kernel<T, true>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((accept_kernel<T, false>), grid, block, 0, st, a);
+}
+
 hipError_t launch_accept(const AcceptArgs &a, int dtype, hipStream_t st) {
-    dim3 grid((unsigned)(a.B * a.T * a.n_chunks)), block(256);
-    if (dtype == MAD_BF16) hipLaunchKernelGGL(accept_kernel<bf16_t>, grid, block, 0, st, a);
-    else hipLaunchKernelGGL(accept_kernel<float>, grid, block, 0, st, a);
+    if (dtype == MAD_BF16) launch_accept_t<bf16_t>(a, st);
+    else launch_accept_t<float>(a, st);
     return hipGetLastError();
 }
 

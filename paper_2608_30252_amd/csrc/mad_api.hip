@@ -658,7 +658,7 @@ int mad_accept_stochastic(const float *p, const float *q, const int32_t *draft_t
     a.B = B;
     a.T = T;
     a.V = V;
-    a.n_chunks = (V + mad::kAcceptChunk - 1) / mad::kAcceptChunk;
+    a.n_chunks = (V + mad::kStochChunk - 1) / mad::kStochChunk;
     a.vec16 = aligned16(p) && (T == 1 || aligned16(q)) && V % 4 == 0;
     return hip_status(mad::launch_stoch(a, (hipStream_t)stream), "stochastic accept launch");
 }

@@ -154,7 +154,8 @@ int prefill_tokens_per_block(int d, int G);
 hipError_t launch_prefill(const PrefillArgs &a, int d, int G, hipStream_t st);
 
 // ---------------------------------------------------------------- accept ----
-constexpr int kAcceptChunk = 8192;   // vocabulary entries per workgroup
+constexpr int kAcceptChunk = 8192;   // vocabulary entries per workgroup, greedy rule
+constexpr int kStochChunk = 2048;    // ... stochastic rule
 constexpr int kAcceptMaxT = 256;     // rows per sequence of the greedy rule (one workgroup applies it)
 static_assert((size_t)kMaxB * kCounterStride * 4 + (size_t)kMaxB * kAcceptMaxT * 8 <= kCounterRegionBytes,
               "greedy-accept counters and row keys fit the counter region");

@@ -127,3 +127,35 @@ def test_workspace_shared_with_decode_and_garbage_past_the_counters():
         np.testing.assert_array_equal(na.cpu().numpy(), na_ref)
         np.testing.assert_array_equal(nx.cpu().numpy(), nx_ref)
     assert int(ws[: 1 << 20].count_nonzero()) == 0   # counters and row keys left at zero
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("V", [8, 24, 1024, 8192, 8200, 9216, 16376, 1, 3, 257, 8191, 8193, 16383])
+def test_vocabularies_ties_and_nan_at_every_place(V, dtype):
+    """A maximum is taken, then its first place; pieces (unaligned: entries) past a chunk repeat its last.  One
+    maximum at the first and last entries and beside each chunk's edge, the same value twice (the lower index
+    wins), a NaN there (it wins, the first of two), a row of -inf, and a row whose maximum is a zero of either
+    sign."""
+    import oracle
+    g = torch.Generator().manual_seed(V)
+    places = sorted({0, min(1, V - 1), V - 1, max(0, V - 2), V // 2, min(8191, V - 1), min(8192, V - 1), max(0, V - 8), max(0, V - 9)})
+    rows = []
+    for a in places:
+        base = torch.randn(V, generator=g)
+        one, two, nan, nans = base.clone(), base.clone(), base.clone(), base.clone()
+        one[a] = 9.0
+        two[a], two[(a + V // 2) % V] = 9.0, 9.0
+        nan[a], nan[(a + 5) % V] = float("nan"), float("inf")
+        nans[a], nans[(a + V // 3) % V] = float("nan"), float("nan")
+        rows += [one, two, nan, nans]
+    rows.append(torch.full((V,), -float("inf")))
+    zeros = -torch.rand(V, generator=g) - 0.5
+    zeros[V // 2], zeros[V - 1] = -0.0, 0.0
+    rows.append(zeros)
+    x = torch.stack(rows).to(dtype)[:, None, :].contiguous()     # T = 1: next_tok is the row's argmax
+    for i in range(0, x.shape[0], 64):
+        part = x[i:i + 64].contiguous()
+        na, nx = _run(part, None)
+        ref, nref = oracle.accept_greedy(part.float().numpy(), np.zeros((part.shape[0], 0), np.int32))
+        np.testing.assert_array_equal(na, ref)
+        np.testing.assert_array_equal(nx, nref)

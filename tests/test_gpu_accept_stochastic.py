@@ -114,3 +114,12 @@ def test_threshold_equality_rejects():
         torch.cuda.synchronize()
         assert int(na.item()) == int(na_ref[0]) == want
         assert int(nx.item()) == int(nx_ref[0])
+
+
+@pytest.mark.parametrize("V", [1, 255, 2047, 2048, 2049, 2052, 4100, 131073, 133124])
+def test_chunk_edges_and_more_chunks_than_lanes(V):
+    # one to three chunks with whole and partial last ones, aligned and not; 65 and 66 chunks: the chunk sums take
+    # two passes of a wave; draws over the whole vocabulary and in its last entries
+    _run(3, 3, V, seed=700 + V)
+    if V > 8:
+        _run(2, 3, V, seed=800 + V, tail=3)
