@@ -96,11 +96,17 @@ __device__ __forceinline__ float prefill_row_sum(float v) {
 constexpr float kLazySum = 16.f;  // rescale threshold of the online softmax: a lane's sum of 8 probabilities
 constexpr float kNoMax = 3e38f;   // minus the reference maximum (log2 units) of a row without keys: 2^(s + this) overflows
 
-// the largest value of the wave, wave-uniform
+// the largest value of the wave, wave-uniform: lane swaps on the vector ALU (six
+// rounds of LDS shuffles took 1 us of a workgroup's prologue)
 __device__ __forceinline__ int wave_max_i32(int v) {
-    #pragma unroll
-    for (int x = 1; x < 64; x *= 2) v = max(v, __shfl_xor(v, x));
-    return __builtin_amdgcn_readfirstlane(v);
+    v = max(v, __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true));    // quad_perm [1, 0, 3, 2]
+    v = max(v, __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true));    // quad_perm [2, 3, 0, 1]
+    v = max(v, __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, true));   // row_half_mirror
+    v = max(v, __builtin_amdgcn_mov_dpp(v, 0x140, 0xF, 0xF, true));   // row_mirror
+    const auto a = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+    v = max((int)a[0], (int)a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+    return __builtin_amdgcn_readfirstlane(max((int)b[0], (int)b[1]));
 }
 
 __device__ __forceinline__ int prefill_slots_after(int t, int S, int ru, int u) {
@@ -148,38 +154,6 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void prefill_kernel(const Pre
     const bf16_t *mv = reinterpret_cast<const bf16_t *>(a.mv) + b * a.m_seq + c * a.m_head;
     const bf16_t *rk = reinterpret_cast<const bf16_t *>(a.rk) + b * a.r_seq + c * a.r_head;
     const bf16_t *rv = reinterpret_cast<const bf16_t *>(a.rv) + b * a.r_seq + c * a.r_head;
-    const bf16_t *qbase = reinterpret_cast<const bf16_t *>(slot_kind ? a.q_slot : a.q_raw) +
-                          (size_t)b * (slot_kind ? a.slot_cap : a.q_cap) * a.Hq * D;
-
-    // ---- this lane's rows: query fragments and visible ranges ----
-    bf16x8_v qf[NB][KST];
-    int m_lim[NB], r_lo[NB], r_hi[NB];
-    #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-        const int j = wave + 4 * i, g = j % G, tb = j / G;
-        const int tok = q0 + tb * 16 + lr;
-        if (tok <= qlast) {
-            const bf16_t *qrow = qbase + ((size_t)tok * a.Hq + c * G + g) * D;
-            #pragma unroll
-            for (int ks = 0; ks < KST; ++ks) qf[i][ks] = *reinterpret_cast<const bf16x8_v *>(qrow + ks * 32 + 8 * lg);
-            if (!slot_kind) {
-                m_lim[i] = tok < S ? tok + 1 : S + prefill_slots_after(tok, S, ru, u);
-                r_lo[i] = max(S, tok - W + 1);
-                r_hi[i] = tok < S ? r_lo[i] : tok + 1;
-            } else {
-                const int bm = S + (tok + 1) * r;
-                m_lim[i] = S + tok + 1;
-                r_lo[i] = max(S, bm - W);
-                r_hi[i] = bm;
-            }
-        } else {
-            #pragma unroll
-            for (int ks = 0; ks < KST; ++ks) qf[i][ks] = bf16x8_v{0, 0, 0, 0, 0, 0, 0, 0};
-            m_lim[i] = 0;
-            r_lo[i] = r_hi[i] = 0;
-        }
-    }
-
     // ---- tile loader: direct loads into LDS, the next tile's into the idle stage ----
     auto tile_base = [&](int t, bool &is_mem, int &end) -> int {
         is_mem = t < n_mem_t;
@@ -224,6 +198,40 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void prefill_kernel(const Pre
             }
         }
     };
+
+    load_tile(0, std::integral_constant<int, 0>());   // in flight while the queries are read
+
+    const bf16_t *qbase = reinterpret_cast<const bf16_t *>(slot_kind ? a.q_slot : a.q_raw) +
+                          (size_t)b * (slot_kind ? a.slot_cap : a.q_cap) * a.Hq * D;
+
+    // ---- this lane's rows: query fragments and visible ranges ----
+    bf16x8_v qf[NB][KST];
+    int m_lim[NB], r_lo[NB], r_hi[NB];
+    #pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int j = wave + 4 * i, g = j % G, tb = j / G;
+        const int tok = q0 + tb * 16 + lr;
+        if (tok <= qlast) {
+            const bf16_t *qrow = qbase + ((size_t)tok * a.Hq + c * G + g) * D;
+            #pragma unroll
+            for (int ks = 0; ks < KST; ++ks) qf[i][ks] = *reinterpret_cast<const bf16x8_v *>(qrow + ks * 32 + 8 * lg);
+            if (!slot_kind) {
+                m_lim[i] = tok < S ? tok + 1 : S + prefill_slots_after(tok, S, ru, u);
+                r_lo[i] = max(S, tok - W + 1);
+                r_hi[i] = tok < S ? r_lo[i] : tok + 1;
+            } else {
+                const int bm = S + (tok + 1) * r;
+                m_lim[i] = S + tok + 1;
+                r_lo[i] = max(S, bm - W);
+                r_hi[i] = bm;
+            }
+        } else {
+            #pragma unroll
+            for (int ks = 0; ks < KST; ++ks) qf[i][ks] = bf16x8_v{0, 0, 0, 0, 0, 0, 0, 0};
+            m_lim[i] = 0;
+            r_lo[i] = r_hi[i] = 0;
+        }
+    }
 
     // the wave's tiles without a mask: the tightest of its rows' ranges
     int mem_full = m_lim[0], lo_full = r_lo[0], hi_full = r_hi[0];
@@ -362,7 +370,6 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void prefill_kernel(const Pre
     // The loads of tile t + 1 go out before tile t is used and have landed by its end (the waits are
     // explicit: the compiler does not count direct loads).  Two tiles a round, so that every LDS
     // address has its stage as a constant.
-    load_tile(0, std::integral_constant<int, 0>());
     wait_vm(0);
     __syncthreads();
     for (int t = 0; t < nt; t += 2) {
