@@ -42,8 +42,8 @@
 // conversions, and nothing else of weight: no maxima (a fifth of the vector work
 // before), no address arithmetic (stage and half are instruction offsets), no
 // staging registers (128 registers: four waves per SIMD instead of three).
-// 32K prefix, 32/8 heads, 2048 slots: 792 -> 639 us; 4 ragged prefixes at d 128,
-// W 128: 492 -> 411 us (two waves per SIMD there: latency-bound).  Measured
+// 32K prefix, 32/8 heads, 2048 slots: 792 -> 612 us; 4 ragged prefixes at d 128,
+// W 128: 492 -> 404 us (two waves per SIMD there: latency-bound).  Measured
 // and not kept: 64 rows per wave (685 us against 703 on long windows, but twice the time
 // with one query head per KV head), 32-key tiles in three stages at d 128 (419 - 426).
 // Query blocks of every unit are dealt round-robin over the units (with a
@@ -188,13 +188,23 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : 2) void prefill_kernel(const Pre
                 lds_stream16_x2<false>(ks, k_off[j], k_off[j + 1], lds0 + ST + j * 1024);
                 lds_stream16_x2<false>(vs, v_off[j], v_off[j + 1], lds0 + ST + C::KTILE + j * 1024);
             }
-        } else {   // rows past the range load a valid row (masked)
+        } else {
+            // rows past the range load a valid row (masked): the pair's offsets from 1 KB before the base, so
+            // that neither is negative once its row is clamped
+            const unsigned char *k1 = reinterpret_cast<const unsigned char *>(ks) - 1024;
+            const unsigned char *v1 = reinterpret_cast<const unsigned char *>(vs) - 1024;
+            uint32_t ko[C::LPW], vo[C::LPW];
             #pragma unroll
             for (int j = 0; j < C::LPW; ++j) {
-                const int inst = wv * C::LPW + j, cidx = inst * 64 + lane, row = cidx / C::CPR, slot = cidx % C::CPR;
-                const int key = min(row, end - 1 - base);
-                lds_stream16(ks + key * D + (slot ^ k_swz<D>(row)) * 8, smem + ST + inst * 1024);
-                lds_stream16(vs + key * D + (slot ^ v_swz<D>(row)) * 8, smem + ST + C::KTILE + inst * 1024);
+                const int cidx = (wave * C::LPW + j) * 64 + lane, row = cidx / C::CPR, slot = cidx % C::CPR;
+                const uint32_t at = min(row, end - 1 - base) * C::RB + ((j & 1) ? 0 : 1024);
+                ko[j] = at + ((slot ^ k_swz<D>(row)) << 4);
+                vo[j] = at + ((slot ^ v_swz<D>(row)) << 4);
+            }
+            #pragma unroll
+            for (int j = 0; j < C::LPW; j += 2) {
+                lds_stream16_x2<false>(k1, ko[j], ko[j + 1], lds0 + ST + j * 1024);
+                lds_stream16_x2<false>(v1, vo[j], vo[j + 1], lds0 + ST + C::KTILE + j * 1024);
             }
         }
     };
