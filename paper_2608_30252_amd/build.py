@@ -70,13 +70,18 @@ def build(verbose: bool = False, out: str = LIB, build_dir: str = BUILD_DIR, def
 
 
 def build_fastcall(verbose: bool = False) -> str:
-    """csrc/fastcall.cpp against the installed torch's headers and libraries (the ones its import loads)."""
+    """csrc/fastcall.cpp against the installed torch's headers and libraries (the ones its import loads).
+
+    NDEBUG leaves out a thread-local debugging counter of pybind11's headers.  It was the module's only thread-local
+    variable, and glibc up to 2.38 sends every access to the thread-local variables of the libraries loaded before
+    (torch's) through its slow path for good once a library with one is loaded behind them: a call through ctypes
+    took 15.0 us of host time without the module and 17.1 with it loaded."""
     import sysconfig
 
     import torch
     from torch.utils.cpp_extension import include_paths
     tmp = FASTCALL + ".tmp"
-    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall",
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-DNDEBUG",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            "-I", os.path.join(HERE, "..", "include"), "-I", sysconfig.get_paths()["include"]]
     for p in include_paths():
