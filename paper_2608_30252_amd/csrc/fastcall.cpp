@@ -138,26 +138,28 @@ void *stream_of(const at::Device &dev) {
     return p;
 }
 
-// the caller's workspace, or the one kept for (device, stream) if it is large enough
+// the caller's workspace, or the one kept for (device, stream) if it is large enough.  It is held until the C entry
+// point has returned: without the interpreter lock another thread may put a larger one in the kept one's place, and
+// memory given back before this call's kernels are enqueued could be another tensor's by the time they run.
 struct Scratch {
+    const Ref held;
     void *p;
     size_t n;
-    Scratch(PyObject *ws, const at::Device &dev, void *stream, size_t bytes) {
+    Scratch(PyObject *ws, const at::Device &dev, void *stream, size_t bytes) : held(of(ws, dev, stream)) {
+        const at::Tensor &t = tensor(held.p);
+        need((size_t)t.numel() >= bytes);
+        p = t.data_ptr();
+        n = (size_t)t.numel();
+    }
+    static PyObject *of(PyObject *ws, const at::Device &dev, void *stream) {   // an owned reference
         if (ws != Py_None) {
-            take(tensor(ws), bytes);
-            return;
+            Py_INCREF(ws);
+            return ws;
         }
         Ref key(Py_BuildValue("(iN)", (int)dev.index(), PyLong_FromVoidPtr(stream)));
         PyObject *w = PyDict_GetItemWithError(g_ws, key.p);
         need(w != nullptr);
-        Ref buf(PyObject_GetAttr(w, s_buf));
-        need(buf.p != Py_None);
-        take(tensor(buf.p), bytes);
-    }
-    void take(const at::Tensor &t, size_t bytes) {
-        need((size_t)t.numel() >= bytes);
-        p = t.data_ptr();
-        n = (size_t)t.numel();
+        return PyObject_GetAttr(w, s_buf);
     }
 };
 

@@ -5,6 +5,10 @@ and takes the ctypes path; the same values in lists take the native one.  Both
 must pass the same arguments on, so every output is bit-identical; and a failed
 check or a return code of the library raises the same error on both.
 """
+import contextlib
+import ctypes
+import weakref
+
 import numpy as np
 import pytest
 import torch
@@ -65,3 +69,40 @@ def test_errors_are_the_same_on_both_paths(as_seq):
     with pytest.raises(ValueError, match="contiguous"):
         mad.draft_decode_attn(q.transpose(0, 1).contiguous().transpose(0, 1), mad.KV(k, k, as_seq([1, 1])), None, None,
                               None, o, l)
+
+
+@contextlib.contextmanager
+def _entry(mad, name, fn):
+    """The native functions call `fn` in place of the C entry point `name` (nothing is enqueued)."""
+    lib, fast = mad._load_library(), mad._fast()
+    stub = ctypes.CFUNCTYPE(ctypes.c_int, *getattr(lib, name).argtypes)(fn)
+    address = lambda n: ctypes.cast(stub if n == name else getattr(lib, n), ctypes.c_void_p).value
+    fast.bind(tuple(address(n) for n in mad._FAST_ENTRIES), mad.KV, mad._default_ws, torch._C._cuda_getCurrentRawStream)
+    try:
+        yield
+    finally:
+        mad._FAST = None
+        mad._fast()
+
+
+def test_kept_workspace_outlives_its_replacement_during_the_call():
+    """The C entry point runs without the interpreter lock, and another thread on the stream may replace the kept
+    workspace meanwhile: the old one's memory must not be given back before the entry point has enqueued its work."""
+    import paper_2608_30252_amd as mad
+    q = torch.zeros(1, 4, 64, dtype=torch.bfloat16, device="cuda")
+    kv = mad.KV(torch.zeros(1, 1, 8, 64, dtype=torch.bfloat16, device="cuda"), torch.zeros(1, 1, 8, 64, dtype=torch.bfloat16, device="cuda"), [3])
+    o, l = torch.empty_like(q), torch.empty(1, 4, device="cuda")
+    mad.draft_decode_attn(q, kv, None, None, None, o, l)   # the workspace of this stream exists from here on
+    torch.cuda.synchronize()
+    kept = mad._default_ws[(q.device.index, torch.cuda.current_stream().cuda_stream)]
+    seen = []
+
+    def replaced(*args):
+        old = weakref.ref(kept.buf)
+        kept.buf = None
+        seen.append(old() is not None)
+        return mad.MAD_OK
+
+    with _entry(mad, "mad_draft_decode_attn", replaced):
+        mad.draft_decode_attn(q, kv, None, None, None, o, l)
+    assert seen == [True]
