@@ -88,11 +88,9 @@ double as_double(PyObject *o) {
     need(PyFloat_CheckExact(o));
     return PyFloat_AS_DOUBLE(o);
 }
-// n or more ints of a list or tuple; the first n
-template <typename I> void ints(PyObject *o, int64_t n, I *out, bool exact = false) {
-    need(PyList_CheckExact(o) || PyTuple_CheckExact(o));
-    const Py_ssize_t len = PySequence_Fast_GET_SIZE(o);
-    need(exact ? len == n : len >= n);
+// the n ints of a list or tuple
+template <typename I> void ints(PyObject *o, int64_t n, I *out) {
+    need((PyList_CheckExact(o) || PyTuple_CheckExact(o)) && PySequence_Fast_GET_SIZE(o) == n);
     PyObject **items = PySequence_Fast_ITEMS(o);
     for (int64_t i = 0; i < n; ++i) {
         const int v = as_int(items[i]);
@@ -208,7 +206,7 @@ PyObject *attn(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const float scale = scale_of(a[7], d);
         uint8_t modes[MAD_MAX_BATCH];
         const bool step = a[9] != Py_None;
-        if (step) ints(a[9], B, modes, true);
+        if (step) ints(a[9], B, modes);
         void *st = stream_of(dev);
         const Scratch ws(a[8], dev, st, g.ws_bytes(MAD_OP_DECODE, B, Hq, (int)Hkv, d, 1, 0));
         const int dt = dtype_code(q);
@@ -241,7 +239,7 @@ PyObject *update(PyObject *, PyObject *const *a, Py_ssize_t n) {
         mad_kv_view *mv = mem.read(a[3], B, &Hkv, d, x);
         need((PyList_CheckExact(a[2]) || PyTuple_CheckExact(a[2])) && PySequence_Fast_GET_SIZE(a[2]) == B);
         int32_t pos[MAD_MAX_UPDATE_ROWS];
-        for (int b = 0; b < B; ++b) ints(PySequence_Fast_ITEMS(a[2])[b], nn, pos + (size_t)b * nn, true);
+        for (int b = 0; b < B; ++b) ints(PySequence_Fast_ITEMS(a[2])[b], nn, pos + (size_t)b * nn);
         uint8_t fire[MAD_MAX_BATCH];
         if (a[4] != Py_None) {
             need((PyList_CheckExact(a[4]) || PyTuple_CheckExact(a[4])) && PySequence_Fast_GET_SIZE(a[4]) == B);
@@ -299,7 +297,7 @@ PyObject *verify_vt(PyObject *, PyObject *const *a, Py_ssize_t n) {
         need(k.stride(0) == vt.stride(0) && k.stride(1) == vt.stride(1));
         need(k.scalar_type() == q.scalar_type() && vt.scalar_type() == q.scalar_type() && k.device() == dev && vt.device() == dev);
         int32_t len[MAD_MAX_BATCH];
-        ints(a[3], B, len, true);
+        ints(a[3], B, len);
         const at::Tensor &out = dense(a[4], dev), &lse = dense(a[5], dev);
         need(out.sizes() == q.sizes() && out.scalar_type() == q.scalar_type());
         need(shape(lse, {B, T, Hq}) && lse.scalar_type() == at::kFloat);
@@ -379,7 +377,7 @@ PyObject *qkv(PyObject *, PyObject *const *a, Py_ssize_t n) {
             xn = t.data_ptr();
         }
         int32_t pos[MAD_MAX_LAYER_ROWS];
-        ints(a[3], R, pos, true);
+        ints(a[3], R, pos);
         const float eps = (float)as_double(a[11]);
         const double base = as_double(a[12]);
         need(PyBool_Check(a[13]));

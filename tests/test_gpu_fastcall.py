@@ -69,6 +69,14 @@ def test_errors_are_the_same_on_both_paths(as_seq):
     with pytest.raises(ValueError, match="contiguous"):
         mad.draft_decode_attn(q.transpose(0, 1).contiguous().transpose(0, 1), mad.KV(k, k, as_seq([1, 1])), None, None,
                               None, o, l)
+    # a length, or a ring start, too many
+    with pytest.raises(IndexError):
+        mad.draft_decode_attn(q, mad.KV(k, k, as_seq([1, 1, 1])), None, None, None, o, l)
+    with pytest.raises(IndexError):
+        mad.draft_decode_attn(q, None, mad.KV(k, k, as_seq([1, 1]), as_seq([0, 0, 0])), None, None, o, l)
+    qv, ov, lv = q[:, None].contiguous(), torch.empty(2, 1, 8, 64, dtype=torch.bfloat16, device="cuda"), l[:, None].contiguous()
+    with pytest.raises(IndexError):
+        mad.verify_attn(qv, mad.KV(k, k, as_seq([1, 1, 1])), ov, lv)
 
 
 @contextlib.contextmanager
