@@ -5,8 +5,9 @@ marshals arguments -- tensor pointers, strides, host length arrays and the
 current HIP stream -- into the C entry points; every step of the path runs in
 the library's HIP kernels.  The ordinary call (plain tensors, outputs given,
 lengths in lists) is marshalled by _fastcall.so in native code; whatever that
-does not handle, failed checks among it, takes the ctypes path below.  PyTorch provides device memory and
-streams.  The library is loaded on first use; if libmad.so is missing that
+does not handle, failed checks among it, takes the ctypes path below, as does
+every call where _fastcall.so cannot be loaded.  PyTorch provides device memory
+and streams.  The library is loaded on first use; if libmad.so is missing that
 first call raises: there is no fallback.
 
 Entry points (same names as the C ABI, without the ``mad_`` prefix):
@@ -18,6 +19,7 @@ Entry points (same names as the C ABI, without the ``mad_`` prefix):
 """
 import ctypes
 import os
+import warnings
 from dataclasses import dataclass
 from typing import Optional, Sequence
 
@@ -92,6 +94,13 @@ _FAST_ENTRIES = ("mad_draft_decode_attn", "mad_draft_step_attn", "mad_memory_upd
                  "mad_linear_residual", "mad_rmsnorm_swiglu", "mad_workspace_bytes")
 
 
+class _CtypesOnly:
+    """In the native module's place where it cannot be loaded: every call takes the ctypes path."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def _fast():
     """The native marshalling module, bound to the loaded library.  Its functions return the C entry
     point's code, or None (nothing enqueued) for a call that the ctypes path has to take."""
@@ -100,9 +109,11 @@ def _fast():
     if _FAST is None:
         try:
             from . import _fastcall
-        except ImportError as e:
-            raise ImportError("_fastcall.so is missing or does not load: build it with "
-                              "`python -m paper_2608_30252_amd.build`") from e
+        except ImportError as e:   # not built, or built for another torch
+            warnings.warn(f"_fastcall.so is missing or does not load ({e}): calls are marshalled through ctypes, about "
+                          "10 us slower; build it with `python -m paper_2608_30252_amd.build`", RuntimeWarning, stacklevel=3)
+            _FAST = _CtypesOnly()
+            return _FAST
         _fastcall.bind(tuple(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _FAST_ENTRIES), KV,
                        _default_ws, torch._C._cuda_getCurrentRawStream)
         _FAST = _fastcall

@@ -1,9 +1,11 @@
 """Properties of the binding's native module as it is built (no GPU)."""
 import os
 import struct
+import sys
 import time
 
 import numpy as np
+import pytest
 import torch
 
 import paper_2608_30252_amd as mad
@@ -25,6 +27,19 @@ def test_native_module_has_no_thread_local_storage():
     PT_LOAD, PT_TLS = 1, 7
     types = _segment_types(os.path.join(os.path.dirname(mad.__file__), "_fastcall.so"))
     assert PT_LOAD in types and PT_TLS not in types
+
+
+def test_without_the_native_module_calls_take_the_ctypes_path(monkeypatch):
+    """libmad.so alone serves every call, as it did before there was a native module; a warning says what is missing."""
+    monkeypatch.setitem(sys.modules, "paper_2608_30252_amd._fastcall", None)   # an import of it raises
+    monkeypatch.delattr(mad, "_fastcall", raising=False)
+    monkeypatch.setattr(mad, "_FAST", None)
+    w = torch.zeros(64, 64, dtype=torch.bfloat16)
+    with pytest.warns(RuntimeWarning, match="_fastcall"):
+        assert mad._fast().linear(w, w, w, w) is None
+    x = torch.zeros(1, 1, 64)
+    with pytest.raises(ValueError, match="w_kv"):   # the ctypes path's own check
+        mad.memory_update(x, x[0], [[0]], mad.KV(torch.zeros(1, 1, 8, 64), torch.zeros(1, 1, 8, 64), [0]))
 
 
 def _us(call, n=500, reps=9):
