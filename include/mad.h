@@ -48,7 +48,7 @@ extern "C" {
 #define MAD_EINVAL (-1)  /* bad pointer, shape, length, capacity or workspace argument */
 #define MAD_ENOTSUP (-2) /* valid but unsupported: head_dim, group size, dtype */
 #define MAD_EHIP (-3)    /* a HIP launch failed; the message carries hipGetErrorString */
-#define MAD_EWS (-4)     /* workspace smaller than mad_workspace_bytes() asks */
+#define MAD_EWS (-4)     /* workspace smaller than the call needs (mad_workspace_bytes) */
 
 #define MAD_F32 0
 #define MAD_BF16 1
@@ -63,6 +63,7 @@ extern "C" {
 #define MAD_OP_VERIFY 2
 #define MAD_OP_ACCEPT 3
 #define MAD_OP_ACCEPT_STOCH 4
+#define MAD_OP_DECODE_LEAST 5
 
 /*
  * A per-sequence, per-KV-head run of key/value rows in device memory.
@@ -383,6 +384,10 @@ int mad_probe_handoff_latency(void *buf, size_t buf_bytes, unsigned long long *c
  *   VERIFY: B, Hq, Hkv, d, T                    (max_keys ignored)
  *   ACCEPT: B, T, max_keys = V                  (Hq, Hkv, d ignored)
  *   ACCEPT_STOCH: B, max_keys = V               (Hq, Hkv, d, T ignored)
+ *   DECODE_LEAST: B, Hq, Hkv, d
+ * A decode call is accepted from DECODE_LEAST on, what its split partials take
+ * (at most 68 KB for each of the B * Hkv units).  With less than DECODE a call
+ * may run another kernel: the same sums in another order.
  * Returns 0 for an unknown op or invalid sizes.  The memory update and the
  * draft-layer maps take no workspace (MAD_OP_UPDATE is 0 bytes).
  */

@@ -30,7 +30,7 @@ LIB_PATH = os.path.join(_HERE, "libmad.so")
 
 MAD_OK, MAD_EINVAL, MAD_ENOTSUP, MAD_EHIP, MAD_EWS = 0, -1, -2, -3, -4
 MAD_F32, MAD_BF16 = 0, 1
-MAD_OP_DECODE, MAD_OP_UPDATE, MAD_OP_VERIFY, MAD_OP_ACCEPT, MAD_OP_ACCEPT_STOCH = 0, 1, 2, 3, 4
+MAD_OP_DECODE, MAD_OP_UPDATE, MAD_OP_VERIFY, MAD_OP_ACCEPT, MAD_OP_ACCEPT_STOCH, MAD_OP_DECODE_LEAST = 0, 1, 2, 3, 4, 5
 MAX_BATCH = 64
 
 _i32p = ctypes.POINTER(ctypes.c_int32)
@@ -293,7 +293,8 @@ def draft_decode_attn(q: torch.Tensor, mem: Optional[KV], win: Optional[KV],
             _check(rc)
             return out, lse
     B, Hq, Hkv, d, out, lse, scale, mv, wv = _decode_args(q, mem, win, k_new, v_new, out, lse, scale)
-    nbytes = workspace_bytes(MAD_OP_DECODE, B, Hq, Hkv, d)
+    # a given workspace has to hold the split partials; the library streams where it holds more
+    nbytes = workspace_bytes(MAD_OP_DECODE if ws is None else MAD_OP_DECODE_LEAST, B, Hq, Hkv, d)
     w = _ws_for(q.device, nbytes, ws)
     rc = _load_library().mad_draft_decode_attn(_ptr(q), B, Hq, Hkv, d, _dtype_code(q), float(scale),
                                    ctypes.byref(mv) if mv is not None else None,
@@ -336,7 +337,8 @@ def draft_step_attn(q: torch.Tensor, mem: Optional[KV], win: Optional[KV], k_new
     B, Hq, Hkv, d, out, lse, scale, mv, wv = _decode_args(q, mem, win, k_new, v_new, out, lse, scale)
     _need(len(new_mode) == B, "new_mode needs one entry per row")
     modes = (ctypes.c_uint8 * B)(*[int(m) for m in new_mode])
-    nbytes = workspace_bytes(MAD_OP_DECODE, B, Hq, Hkv, d)
+    # a given workspace has to hold the split partials; the library streams where it holds more
+    nbytes = workspace_bytes(MAD_OP_DECODE if ws is None else MAD_OP_DECODE_LEAST, B, Hq, Hkv, d)
     w = _ws_for(q.device, nbytes, ws)
     rc = _load_library().mad_draft_step_attn(_ptr(q), B, Hq, Hkv, d, _dtype_code(q), float(scale),
                                              ctypes.byref(mv) if mv is not None else None,

@@ -767,10 +767,18 @@ size_t decode_part_stride(int d, int G) {
     return ((size_t)decode_max_splits(d, G) * G * (d + 2) + 63) / 64 * 64;
 }
 
+// What the split kernel's partials take: all that a call has to be given.
+size_t decode_split_bytes(int B, int Hq, int Hkv, int d) {
+    return kCounterRegionBytes + (size_t)B * Hkv * decode_part_stride(d, Hq / Hkv) * 4 + 256;
+}
+
+// ... and what serves either kernel.  The stream kernel's pieces take more for few (sequence, KV head) units only
+// (2 units of 16 heads at d 128: 2.15 MB against 133 KB), so a workspace sized for more heads may hold the partials
+// of fewer, but not their pieces: such a call runs on the split kernel.
 size_t decode_ws_bytes(int B, int Hq, int Hkv, int d) {
-    const size_t splits = (size_t)B * Hkv * decode_part_stride(d, Hq / Hkv) * 4 + 256;
-    const size_t pieces = stream_part_bytes(B * Hkv, Hq / Hkv, d);
-    return kCounterRegionBytes + (splits > pieces ? splits : pieces);
+    const size_t splits = decode_split_bytes(B, Hq, Hkv, d);
+    const size_t pieces = kCounterRegionBytes + stream_part_bytes(B * Hkv, Hq / Hkv, d);
+    return splits > pieces ? splits : pieces;
 }
 
 template <typename T, int D, int G, int NSUB>

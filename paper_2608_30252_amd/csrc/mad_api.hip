@@ -90,6 +90,9 @@ size_t mad_workspace_bytes(int op, int B, int Hq, int Hkv, int d, int T, int max
         case MAD_OP_DECODE:
             if (B < 1 || Hq < 1 || Hkv < 1 || Hq % Hkv || (d != 64 && d != 128)) return 0;
             return mad::decode_ws_bytes(B, Hq, Hkv, d);
+        case MAD_OP_DECODE_LEAST:
+            if (B < 1 || Hq < 1 || Hkv < 1 || Hq % Hkv || (d != 64 && d != 128)) return 0;
+            return mad::decode_split_bytes(B, Hq, Hkv, d);
         case MAD_OP_VERIFY:
             if (B < 1 || Hq < 1 || Hkv < 1 || Hq % Hkv || (d != 64 && d != 128) || T < 1) return 0;
             return mad::verify_ws_bytes(B, Hq, Hkv, d, T);
@@ -147,7 +150,7 @@ int decode_impl(const void *q, int B, int Hq, int Hkv, int d, int dtype, float s
         a.seq[b].w = mode[b];
         n_keys[b] = a.seq[b].x + a.seq[b].y + (mode[b] ? 1 : 0);
     }
-    // long bf16 launches stream; without the workspace that takes they run as the short ones do
+    // long bf16 launches stream; without the workspace that takes they run on the split kernel as the short ones do
     const size_t part = mad::stream_part_bytes(B * Hkv, G, d);
     if (mad::decode_streams(B, Hkv, G, d, dtype, n_keys) && ws && aligned16(ws) &&
         ws_bytes >= mad::kCounterRegionBytes + part) {
@@ -182,7 +185,7 @@ int decode_impl(const void *q, int B, int Hq, int Hkv, int d, int dtype, float s
         return hip_status(mad::launch_stream(s, d, (hipStream_t)stream), "decode launch");
     }
     mad::DecodePlan p = mad::plan_decode(B, Hkv, G, d, dtype, n_keys);
-    size_t need = p.n_splits > 1 ? mad::decode_ws_bytes(B, Hq, Hkv, d) : 0;
+    size_t need = p.n_splits > 1 ? mad::decode_split_bytes(B, Hq, Hkv, d) : 0;
     if (need > 0) {
         if (!ws) return fail(MAD_EWS, "workspace required (%zu bytes)", need);
         if (ws_bytes < need) return fail(MAD_EWS, "workspace %zu bytes < %zu", ws_bytes, need);
@@ -289,7 +292,7 @@ int mad_draft_decode_attn_noalloc(const void *q, int B, int Hq, int Hkv, int d, 
     if (B < 1 || B > MAD_MAX_BATCH) return fail(MAD_EINVAL, "B=%d outside [1, %d]", B, MAD_MAX_BATCH);
     int rc = check_heads(B, Hq, Hkv, d, dtype);
     if (rc) return rc;
-    const size_t need = mad::decode_ws_bytes(B, Hq, Hkv, d);
+    const size_t need = mad::decode_split_bytes(B, Hq, Hkv, d);
     if (need > kNoallocScratchBytes)
         return fail(MAD_EINVAL, "B=%d, Hkv=%d, d=%d need %zu bytes of scratch, above the %zu-byte limit of the "
                     "no-allocation entry point (use mad_draft_decode_attn with a workspace)", B, Hkv, d, need,

@@ -55,6 +55,7 @@ bool decode_streams(int B, int Hkv, int G, int d, int dtype, const int *n_keys);
 DecodePlan plan_decode(int B, int Hkv, int G, int d, int dtype, const int *n_keys);
 int decode_max_splits(int d, int G);
 size_t decode_part_stride(int d, int G);
+size_t decode_split_bytes(int B, int Hq, int Hkv, int d);
 size_t decode_ws_bytes(int B, int Hq, int Hkv, int d);
 hipError_t launch_decode(const DecodeArgs &a, int dtype, int d, int G, hipStream_t st);
 

@@ -783,7 +783,7 @@ size_t stream_part_bytes(int units, int rows, int d) {
 size_t verify_ws_bytes(int B, int Hq, int Hkv, int d, int T) {
     const size_t bf = kCounterRegionBytes + stream_part_bytes(B * Hkv, T * (Hq / Hkv), d);
     // fp32 verify runs the decode kernel once per sequence, its T query rows as the rows
-    const size_t f32 = decode_ws_bytes(T, Hq, Hkv, d);
+    const size_t f32 = decode_split_bytes(T, Hq, Hkv, d);
     return bf > f32 ? bf : f32;
 }
 

@@ -67,6 +67,17 @@ def test_workspace_sizes(mad):
     assert ws(99, 1, 1, 1, 64) == 0
 
 
+def test_least_decode_workspace(mad):
+    ws = mad.workspace_bytes
+    for heads in ((32, 8), (32, 2), (16, 1), (64, 8), (8, 8)):   # the split partials: at most 68 KB a unit
+        for d in (64, 128):
+            least = ws(mad.MAD_OP_DECODE_LEAST, 1, *heads, d)
+            assert (1 << 20) < least <= (1 << 20) + heads[1] * (68 << 10) + 256
+            assert least <= ws(mad.MAD_OP_DECODE, 1, *heads, d)
+            assert ws(mad.MAD_OP_DECODE_LEAST, 3, *heads, d) > least
+    assert ws(mad.MAD_OP_DECODE_LEAST, 1, 30, 8, 64) == 0
+
+
 def _last_error(mad):
     return mad._load_library().mad_last_error().decode()
 

@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 
 
 def _case(dtype, B, Hq, Hkv, d, mlen, wlen, wcap, wstart, new=True, seed=0, mcap=None, peaky=0.0,
-          mem=True):
+          mem=True, ws_bytes=None):
     import paper_2608_30252_amd as mad
     from paper_2608_30252_amd import synth
     dev = torch.device("cuda")
@@ -69,7 +69,8 @@ def _case(dtype, B, Hq, Hkv, d, mlen, wlen, wcap, wstart, new=True, seed=0, mcap
     win = mad.KV(g["wk"], g["wv"], wlen, wstart)
     out = guarded(torch.full_like(g["q"], 3.0), 3.0)
     lse = guarded(torch.full((B, Hq), 5.0, device=dev), 5.0)
-    mad.draft_decode_attn(g["q"], memkv, win, g["kn"] if new else None, g["vn"] if new else None, out, lse)
+    ws = guarded(torch.zeros(ws_bytes, dtype=torch.uint8, device=dev), 7) if ws_bytes else None
+    mad.draft_decode_attn(g["q"], memkv, win, g["kn"] if new else None, g["vn"] if new else None, out, lse, ws=ws)
     torch.cuda.synchronize()
     for buf, pad, n_, before in guards:
         for band in (slice(0, pad), slice(pad + n_, 2 * pad + n_)):
@@ -263,6 +264,26 @@ def test_deterministic():
 def test_long_and_many_headed_launches_stream(B, Hq, Hkv, d, mlen, wlen, wcap, wstart, new, mem):
     for _ in range(2):   # the second call finds the counters the first left
         _case(torch.bfloat16, B, Hq, Hkv, d, mlen, wlen, wcap, wstart, new=new, seed=40 + d + B, mem=mem)
+
+
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,d,keys,sized_for", [
+    (torch.bfloat16, 1, 32, 2, 128, 700, None),       # several splits
+    (torch.bfloat16, 1, 32, 2, 64, 4000, None),       # would stream with the pieces' workspace
+    (torch.bfloat16, 1, 32, 2, 128, 3000, (32, 8)),   # sized for more KV heads
+    (torch.bfloat16, 1, 64, 8, 128, 9000, None),
+    (torch.float32, 1, 32, 2, 128, 1500, None),
+])
+def test_the_split_partials_workspace_serves_the_call(dtype, B, Hq, Hkv, d, keys, sized_for):
+    """A call takes a workspace of its split partials alone, and one sized for more heads, whichever kernel the larger
+    workspace of its own size would choose; the bytes around it stay untouched, and one byte less is refused."""
+    import paper_2608_30252_amd as mad
+    least = mad.workspace_bytes(mad.MAD_OP_DECODE_LEAST, B, Hq, Hkv, d)
+    n = mad.workspace_bytes(mad.MAD_OP_DECODE, B, *sized_for, d) if sized_for else least
+    _case(dtype, B, Hq, Hkv, d, keys // 3, keys - keys // 3, keys, 5, seed=60 + d, ws_bytes=n)
+    q = torch.zeros(B, Hq, d, dtype=dtype, device="cuda")
+    k = torch.zeros(B, Hkv, keys, d, dtype=dtype, device="cuda")
+    with pytest.raises(ValueError, match="workspace"):
+        mad.draft_decode_attn(q, mad.KV(k, k, [keys] * B), None, ws=torch.zeros(least - 1, dtype=torch.uint8, device="cuda"))
 
 
 def test_one_workspace_serves_calls_of_different_shapes():
