@@ -80,7 +80,7 @@ bool update_uses_gemv(int R, int D, int dtype);
 constexpr int kStreamWGs = 256;   // workgroups of a launch: one per CU
 __host__ __device__ constexpr int stream_slab(int d) { return d == 128 ? 64 : 128; }   // keys per slab (32 KB of K + V)
 
-constexpr int kMergeBytes = 128 << 10;   // LDS a merging workgroup fills with pieces at a time
+constexpr int kMergeInLaunch = 48 << 10;   // bytes of a unit's pieces that a workgroup of the launch itself merges (plan_stream)
 
 // verify over a cache of K and V rows; over K rows and V^T (one run of cap keys per feature);
 // the draft's decode: memory rows, window ring, new token (T = 1)
@@ -97,7 +97,7 @@ struct StreamArgs {
     int cap, Hq, Hkv, G, T, kind;
     int n_wg, base, rem;      // workgroup w runs base (+ 1 for w < rem) consecutive slabs
     int by_unit;              // 1: instead, the workgroups of a row's units split each unit evenly
-    int B, merge_nr;          // merge_nr > 0: the pieces are merged by a second launch, merge_nr rows a workgroup
+    int B, merge2;            // merge2: the pieces are merged by a second launch
     int rows, wgs;            // slabs, and by_unit workgroups, of one KV head over all rows
     // per row: keys, -, workgroups (by_unit) and slabs of the rows before it (one KV head); past the last row: the end
     int4 row[kMaxB];          // (draft: memory rows, window rows, ...)

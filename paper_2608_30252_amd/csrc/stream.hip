@@ -39,6 +39,8 @@
 // across units: the next unit's slabs and its query rows (direct loads into a
 // small LDS area, older than the unit's first slab) are in flight while the
 // current unit finishes.
+#include <type_traits>
+
 #include "mad_device.h"
 #include "mad_internal.h"
 
@@ -77,7 +79,7 @@ struct StreamCfg {
     static constexpr int XPASS = KS * RP * D * 4 > STAGE ? 2 : 1;   // passes of the key groups' exchange through one stage
     static_assert((NST * STAGE & (NST * STAGE - 1)) == 0 && IPW % 2 == 0 && KS * NB <= NWV && KPG % 32 == 0, "waves");
     static_assert(KS * RP * D * 4 <= XPASS * STAGE, "the key groups' exchange fits one stage");
-    static_assert(SMEM + 64 <= 160 * 1024, "LDS");
+    static_assert(SMEM + 2 * MAD_MAX_VERIFY_ROWS * 4 + 64 <= 160 * 1024, "LDS, with the kernel's static arrays");
 };
 
 typedef short v4s_t __attribute__((ext_vector_type(4)));
@@ -93,7 +95,7 @@ struct StreamCtx {
     uint64_t q, k, v, out, lse, part, counters;
     int64_t seq, head;
     float cs;
-    int cap, Hq, Hkv, G, T, base, rem, by_unit, merge_nr, rows, wgs;   // rows, wgs: slabs and (by_unit) workgroups of one KV head over all rows
+    int cap, Hq, Hkv, G, T, base, rem, by_unit, merge2, rows, wgs;   // rows, wgs: slabs and (by_unit) workgroups of one KV head over all rows
     int4 rec;   // lane b: row b's record
     __device__ __forceinline__ int tile0(int b) const { return __builtin_amdgcn_readlane(rec.w, b); }
     __device__ __forceinline__ int slabs(int b) const { return (b == kMaxB - 1 ? rows : tile0(b + 1)) - tile0(b); }
@@ -109,11 +111,11 @@ __device__ __forceinline__ StreamCtx load_ctx(const StreamArgs &a) {
     x.seq = a.seq; x.head = a.head;
     x.cs = a.scale_log2;
     x.cap = a.cap; x.Hq = a.Hq; x.Hkv = a.Hkv; x.G = a.G; x.T = a.T; x.base = a.base; x.rem = a.rem;
-    x.by_unit = a.by_unit; x.merge_nr = a.merge_nr; x.rows = a.rows; x.wgs = a.wgs;
+    x.by_unit = a.by_unit; x.merge2 = a.merge2; x.rows = a.rows; x.wgs = a.wgs;
     asm volatile("" : "+s"(x.q), "+s"(x.k), "+s"(x.v), "+s"(x.out), "+s"(x.lse), "+s"(x.part),
                  "+s"(x.counters), "+s"(x.seq), "+s"(x.head), "+s"(x.cs));
     asm volatile("" : "+s"(x.cap), "+s"(x.Hq), "+s"(x.Hkv), "+s"(x.G), "+s"(x.T), "+s"(x.base), "+s"(x.rem),
-                 "+s"(x.by_unit), "+s"(x.merge_nr), "+s"(x.rows), "+s"(x.wgs));
+                 "+s"(x.by_unit), "+s"(x.merge2), "+s"(x.rows), "+s"(x.wgs));
     return x;
 }
 
@@ -160,26 +162,26 @@ __device__ __forceinline__ size_t out_head(const StreamCtx &a, int u, int row) {
     return ((size_t)b * a.T + tt) * a.Hq + (size_t)c * a.G + (row - tt * a.G);
 }
 
-// Log-sum-exp merge of rows [ra, ra + nr) of unit u from its pieces as they lie
-// in LDS, by a workgroup of 512 threads: eight lanes per row turn the pieces'
+// Log-sum-exp merge of the nr rows of unit u from its np pieces as they lie in
+// LDS, by a workgroup of 512 threads: eight lanes per row turn the pieces'
 // (max, sum) into weights, then (behind a barrier) one thread per feature quad.
-// Piece p's o rows are at so + p * po bytes, its (max, sum) pairs at sm + p * pm.
+// Piece p's o rows are at so + p * po bytes, its (max, sum) pairs at sm + p * po.
 template <int D>
 struct MergeJob {
-    int u, np, ra, nr;
+    int u, np, nr;
     unsigned char *so, *sm;
-    int po, pm;
+    int po;
     float *sinv;   // [nr]
 
     __device__ __forceinline__ void weights(const StreamCtx &a) const {
         for (int r = threadIdx.x >> 3; r < nr; r += 64) {
             const int l8 = threadIdx.x & 7;
             float M = -INFINITY, L = 0.f;
-            for (int p = l8; p < np; p += 8) M = fmaxf(M, reinterpret_cast<const float2 *>(sm + p * pm)[r].x);
+            for (int p = l8; p < np; p += 8) M = fmaxf(M, reinterpret_cast<const float2 *>(sm + p * po)[r].x);
             M = group_max<8>(M);
             const float mr = M == -INFINITY ? 0.f : M;
             for (int p = l8; p < np; p += 8) {
-                float2 *v = reinterpret_cast<float2 *>(sm + p * pm) + r;
+                float2 *v = reinterpret_cast<float2 *>(sm + p * po) + r;
                 const float wt = __builtin_amdgcn_exp2f(v->x - mr);
                 L = fmaf(wt, v->y, L);
                 v->x = wt;
@@ -187,7 +189,7 @@ struct MergeJob {
             L = group_sum<8>(L);
             if (l8 == 0) {
                 sinv[r] = L > 0.f ? 1.f / L : 0.f;
-                if (a.lse) bits_ptr<float>(a.lse)[out_head(a, u, ra + r)] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
+                if (a.lse) bits_ptr<float>(a.lse)[out_head(a, u, r)] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
             }
         }
     }
@@ -198,12 +200,12 @@ struct MergeJob {
             #pragma unroll 8
             for (int p = 0; p < np; ++p) {
                 const f32x4_v v = *reinterpret_cast<const f32x4_v *>(so + p * po + x * 16);
-                const float wt = reinterpret_cast<const float2 *>(sm + p * pm)[r].x;
+                const float wt = reinterpret_cast<const float2 *>(sm + p * po)[r].x;
                 #pragma unroll
                 for (int e = 0; e < 4; ++e) y[e] = fmaf(wt, v[e], y[e]);
             }
             const float inv = sinv[r];
-            *reinterpret_cast<uint2 *>(bits_ptr<bf16_t>(a.out) + out_head(a, u, ra + r) * D + (x % (D / 4)) * 4) =
+            *reinterpret_cast<uint2 *>(bits_ptr<bf16_t>(a.out) + out_head(a, u, r) * D + (x % (D / 4)) * 4) =
                 make_uint2(pack_bf16x2(y[0] * inv, y[1] * inv), pack_bf16x2(y[2] * inv, y[3] * inv));
         }
     }
@@ -214,42 +216,6 @@ struct MergeJob {
 __device__ __forceinline__ void load_pieces(const float *src, int bytes, unsigned char *lds) {
     for (int x = (threadIdx.x >> 6) * 1024; x < bytes; x += 8192)
         lds_stream16_coherent(reinterpret_cast<const unsigned char *>(src) + min(x + (int)(threadIdx.x & 63) * 16, bytes - 16), lds + x);
-}
-
-// Rows [r0, r1) of unit u where its pieces are more than kMergeBytes: as many
-// rows at a time as fit, sml 4 KB for their (max, sum).
-template <int D>
-__device__ __forceinline__ void merge_rows(const StreamCtx &a, int u, UnitPieces up, int r0, int r1, unsigned char *smem,
-                                           float2 *sml) {
-    __shared__ float sinv[MAD_MAX_VERIFY_ROWS];
-    const int tid = threadIdx.x, R = a.T * a.G, np = up.np, pf = piece_floats(R, D);
-    const float *part = bits_ptr<const float>(a.part) + (size_t)up.p0 * pf;
-    const int most = kMergeBytes / (np * D * 4);   // at least 1: np <= kStreamWGs
-    for (int ra = r0; ra < r1; ra += most) {
-        const int nr = min(most, r1 - ra), q = nr * (D / 4), total = np * q, dp = 512 / q, dx = 512 - dp * q;
-        const int mp = tid / nr;   // the (max, sum) pairs, one a thread: np * nr <= 512
-        const uint64_t ml = mp < np ? load_agent64(reinterpret_cast<const uint64_t *>(part + (size_t)mp * pf + R * D) + ra + (tid - mp * nr)) : 0;
-        __syncthreads();   // earlier readers of smem and sml are done
-        // 16-byte chunk x of [np][q]: x and its (piece, offset) advance by 512 a step; the last step's surplus lanes read the last chunk
-        int pc = tid / q, off = tid - pc * q;
-        for (int x0 = tid & ~63; x0 < total; x0 += 512) {
-            const bool in = pc < np;
-            lds_stream16_coherent(part + (size_t)(in ? pc : np - 1) * pf + ra * D + (in ? off : q - 1) * 4, smem + x0 * 16);
-            pc += dp;
-            off += dx;
-            if (off >= q) {
-                off -= q;
-                ++pc;
-            }
-        }
-        if (mp < np) sml[tid] = make_float2(__uint_as_float((uint32_t)ml), __uint_as_float((uint32_t)(ml >> 32)));
-        __syncthreads();
-        const MergeJob<D> j = {u, np, ra, nr, smem, reinterpret_cast<unsigned char *>(sml), q * 16, nr * 8, sinv};
-        j.weights(a);
-        wait_vm(0);
-        __syncthreads();
-        j.sums(a);
-    }
 }
 
 template <int D, int NB, int KIND>
@@ -649,7 +615,7 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
     }
     MAD_TRACE_SAVE_T0(mad_trace_verify);
     MAD_TRACE(mad_trace_verify, 1);
-    if ((pu0 < 0 && pu1 < 0) || a.merge_nr > 0) return;
+    if ((pu0 < 0 && pu1 < 0) || a.merge2) return;
 
     // ---- arrivals; the last workgroup at a unit merges its pieces, both of its units' (where it is
     // last at both) behind one round trip ----
@@ -671,42 +637,100 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
     MAD_TRACE(mad_trace_verify, 3);
     const int pf = piece_floats(R, D);
     const float *part = bits_ptr<const float>(a.part);
-    float2 *sml = reinterpret_cast<float2 *>(smem + C::OFF_Q);
     const int last = (s_last[0] ? 1 : 0) + (s_last[1] ? 2 : 0);
     if (last == 0) return;
     const int bytes0 = (last & 1) ? up0.np * pf * 4 : 0, bytes1 = (last & 2) ? up1.np * pf * 4 : 0;
-    const int at1 = (bytes0 + 1023) & ~1023;
-    if (at1 + bytes1 <= kMergeBytes) {
-        __shared__ float sinv[2 * MAD_MAX_VERIFY_ROWS];
-        if (last & 1) load_pieces(part + (size_t)up0.p0 * pf, bytes0, smem);
-        if (last & 2) load_pieces(part + (size_t)up1.p0 * pf, bytes1, smem + at1);
-        const MergeJob<D> j0 = {pu0, up0.np, 0, R, smem, smem + R * D * 4, pf * 4, pf * 4, sinv};
-        const MergeJob<D> j1 = {pu1, up1.np, 0, R, smem + at1, smem + at1 + R * D * 4, pf * 4, pf * 4, sinv + R};
-        wait_vm(0);
-        __syncthreads();
-        if (last & 1) j0.weights(a);
-        if (last & 2) j1.weights(a);
-        __syncthreads();
-        if (last & 1) j0.sums(a);
-        if (last & 2) j1.sums(a);
-    } else {
-        if (last & 1) merge_rows<D>(a, pu0, up0, 0, R, smem, sml);
-        if (last & 2) merge_rows<D>(a, pu1, up1, 0, R, smem, sml);
-    }
+    const int at1 = (bytes0 + 1023) & ~1023;   // both fit: plan_stream gives units of more than kMergeInLaunch a second launch
+    static_assert(2 * kMergeInLaunch + 1024 <= C::OFF_Q, "two units' pieces fit the ring");
+    __shared__ float sinv[2 * MAD_MAX_VERIFY_ROWS];
+    if (last & 1) load_pieces(part + (size_t)up0.p0 * pf, bytes0, smem);
+    if (last & 2) load_pieces(part + (size_t)up1.p0 * pf, bytes1, smem + at1);
+    const MergeJob<D> j0 = {pu0, up0.np, R, smem, smem + R * D * 4, pf * 4, sinv};
+    const MergeJob<D> j1 = {pu1, up1.np, R, smem + at1, smem + at1 + R * D * 4, pf * 4, sinv + R};
+    wait_vm(0);
+    __syncthreads();
+    if (last & 1) j0.weights(a);
+    if (last & 2) j1.weights(a);
+    __syncthreads();
+    if (last & 1) j0.sums(a);
+    if (last & 2) j1.sums(a);
     MAD_TRACE(mad_trace_verify, 4);
 }
 
-// The merge as a launch of its own, one workgroup per unit and merge_nr rows
-// (a workgroup past the unit's rows, or at a unit in one piece, has nothing to do).
+// The merge as a launch of its own, one workgroup per unit and query row: NG
+// groups of D/4 threads, a feature quad each, take every NG-th piece.  A thread
+// issues the loads of up to U pieces with their (max, sum) at once and folds
+// them on its own, so the chain is one round trip, an exponential per piece
+// and one exchange between the groups.
 template <int D>
-__global__ __launch_bounds__(512, 1) void stream_merge_kernel(const StreamArgs args) {
-    extern __shared__ __align__(16) unsigned char smem[];
+__global__ __launch_bounds__(256) void stream_merge_kernel(const StreamArgs args) {
+    constexpr int FQ = D / 4, NG = 256 / FQ;
+    __shared__ f32x4_v s_y[NG][FQ];
+    __shared__ float2 s_ml[NG];
     const StreamCtx a = load_ctx(args);
-    const int u = blockIdx.x, r0 = blockIdx.y * a.merge_nr;
-    const int R = a.T * a.G;
-    const UnitPieces p = unit_pieces(a, u);
-    if (p.np == 1 || r0 >= R) return;
-    merge_rows<D>(a, u, p, r0, min(R, r0 + a.merge_nr), smem, reinterpret_cast<float2 *>(smem + kMergeBytes));
+    const int u = blockIdx.x, r = blockIdx.y, R = a.T * a.G;
+    const UnitPieces up = unit_pieces(a, u);
+    if (up.np == 1) return;   // finished by its workgroup
+    const int fq = threadIdx.x % FQ, grp = threadIdx.x / FQ, pf = piece_floats(R, D);
+    const float *po = bits_ptr<const float>(a.part) + (size_t)up.p0 * pf + r * D + fq * 4;
+    const float *pm = bits_ptr<const float>(a.part) + (size_t)up.p0 * pf + R * D + r * 2;
+    float M = -INFINITY, L = 0.f;
+    f32x4_v y = f32x4_v{0.f, 0.f, 0.f, 0.f};
+    auto fold = [&](int p0, auto n_const) {
+        constexpr int U = decltype(n_const)::value;
+        f32x4_v v[U];
+        float2 ml[U];
+        #pragma unroll
+        for (int k = 0; k < U; ++k) {   // past the unit's pieces: the last one again, weighted 0
+            const size_t at = (size_t)min(p0 + k * NG, up.np - 1) * pf;
+            ml[k] = *reinterpret_cast<const float2 *>(pm + at);
+            v[k] = *reinterpret_cast<const f32x4_v *>(po + at);
+        }
+        float mn = M;
+        #pragma unroll
+        for (int k = 0; k < U; ++k) mn = fmaxf(mn, ml[k].x);
+        const float mr = mn == -INFINITY ? 0.f : mn, c = __builtin_amdgcn_exp2f(M - mr);
+        L *= c;
+        y *= c;
+        #pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const float wt = p0 + k * NG < up.np ? __builtin_amdgcn_exp2f(ml[k].x - mr) : 0.f;
+            L = fmaf(wt, ml[k].y, L);
+            #pragma unroll
+            for (int e = 0; e < 4; ++e) y[e] = fmaf(wt, v[k][e], y[e]);
+        }
+        M = mn;
+    };
+    if (up.np <= NG) {
+        fold(grp, std::integral_constant<int, 1>());
+    } else if (up.np <= 4 * NG) {
+        fold(grp, std::integral_constant<int, 4>());
+    } else {
+        for (int p = grp; p < up.np; p += 8 * NG) fold(p, std::integral_constant<int, 8>());
+    }
+    s_y[grp][fq] = y;
+    if (fq == 0) s_ml[grp] = make_float2(M, L);
+    __syncthreads();
+    if (threadIdx.x >= FQ) return;
+    float w[NG];
+    M = s_ml[0].x;
+    #pragma unroll
+    for (int k = 1; k < NG; ++k) M = fmaxf(M, s_ml[k].x);
+    const float mr = M == -INFINITY ? 0.f : M;
+    L = 0.f;
+    y = f32x4_v{0.f, 0.f, 0.f, 0.f};
+    #pragma unroll
+    for (int k = 0; k < NG; ++k) {
+        w[k] = __builtin_amdgcn_exp2f(s_ml[k].x - mr);
+        L = fmaf(w[k], s_ml[k].y, L);
+        #pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] = fmaf(w[k], s_y[k][fq][e], y[e]);
+    }
+    const float inv = L > 0.f ? 1.f / L : 0.f;
+    const size_t head = out_head(a, u, r);
+    *reinterpret_cast<uint2 *>(bits_ptr<bf16_t>(a.out) + head * D + fq * 4) =
+        make_uint2(pack_bf16x2(y[0] * inv, y[1] * inv), pack_bf16x2(y[2] * inv, y[3] * inv));
+    if (a.lse && fq == 0) bits_ptr<float>(a.lse)[head] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
 }
 
 // ------------------------------------------------------------------ host ----
@@ -740,7 +764,7 @@ void plan_stream(StreamArgs &a, int B, int Hkv, int d, const int *n_keys) {
     const int64_t total = rows * Hkv;
     a.B = B;
     a.Hkv = Hkv;
-    a.merge_nr = 0;
+    a.merge2 = 0;
     const bool whole = (int64_t)B * Hkv > kCounterLines || total > 0x3fffffff;   // a unit each
     a.n_wg = total < kStreamWGs ? (int)total : kStreamWGs;
     a.base = whole ? 1 : (int)(total / a.n_wg);
@@ -768,11 +792,14 @@ void plan_stream(StreamArgs &a, int B, int Hkv, int d, const int *n_keys) {
         np_max = (nt_max - 1) / a.base + 2;
         np_max = np_max > a.n_wg ? a.n_wg : np_max;
     }
-    // a unit in np pieces merges np T G d floats.  Up to two LDS fulls the last workgroup there does it
-    // in the launch (4 us at 10 pieces of 20 rows, d 128); more are spread over a second launch (5.8 us at
-    // 33 pieces of 40 rows, six LDS fulls)
+    // A unit's pieces up to kMergeInLaunch are merged by the last workgroup at it; larger ones by a second
+    // launch, which costs 2 - 3 us but spreads over the CUs what one workgroup does serially (32/8 heads, d 128,
+    // 5 queries, 1 sequence: 1000 keys, 16 pieces of 10 KB, 13.4 -> 8.4 us; 4100 keys, 22 pieces, 17.9 -> 11.4;
+    // 32773 keys, 32 pieces, 29.5 -> 26.9).  Either side of the line: 4 pieces, 42 KB, of 8 sequences of 2000
+    // keys 18.4 us in the launch, 18.7 in two; 32 pieces of 4 rows, 64 KB, of a decode of 32768 keys at d 128
+    // 28.1 and 26.8.
     const int64_t bytes = (int64_t)np_max * piece_floats(a.T * a.G, d) * 4;
-    a.merge_nr = bytes > 2 * kMergeBytes ? kMergeBytes / (np_max * d * 4) / 4 + 1 : 0;
+    a.merge2 = bytes > kMergeInLaunch ? 1 : 0;
 }
 
 // the pieces of a launch's units: at most one per workgroup and unit
@@ -815,15 +842,14 @@ static hipError_t launch_d(const StreamArgs &a, hipStream_t st) {
 
 template <int D>
 static hipError_t launch_merge(const StreamArgs &a, hipStream_t st) {
-    const int chunks = (a.T * a.G + a.merge_nr - 1) / a.merge_nr;
-    hipLaunchKernelGGL((stream_merge_kernel<D>), dim3((unsigned)(a.B * a.Hkv), (unsigned)chunks), dim3(512), kMergeBytes + 4096, st, a);
+    hipLaunchKernelGGL((stream_merge_kernel<D>), dim3((unsigned)(a.B * a.Hkv), (unsigned)(a.T * a.G)), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
 hipError_t launch_stream(const StreamArgs &a, int d, hipStream_t st) {
     if (d != 64 && d != 128) return hipErrorInvalidValue;
     const hipError_t e = d == 64 ? launch_d<64>(a, st) : launch_d<128>(a, st);
-    if (e != hipSuccess || a.merge_nr == 0) return e;
+    if (e != hipSuccess || a.merge2 == 0) return e;
     return d == 64 ? launch_merge<64>(a, st) : launch_merge<128>(a, st);
 }
 

@@ -204,3 +204,20 @@ def test_runs_of_slabs_over_ragged_units(B, T, Hq, Hkv, d, lo, hi, layout):
     for _ in range(2):   # the second call finds the counters the first left
         out, lse = _run(q, k, v, length, layout)
     _check(q, k, v, length, out, lse)
+
+
+@pytest.mark.parametrize("layout", LAYOUTS)
+@pytest.mark.parametrize("d,slab", [(64, 128), (128, 64)])
+@pytest.mark.parametrize("T,G,slabs", [
+    (1, 1, 2), (1, 1, 100),                    # pieces of one row, merged in the launch
+    (4, 4, 5), (4, 4, 12),                     # 16 rows: the last sizes in the launch (d 128, d 64) and the first past it
+    (5, 8, 8), (5, 8, 9), (5, 8, 16), (5, 8, 17),   # a second launch: one piece a thread group (8 groups at d 128, 16 at d 64), and one more
+    (5, 8, 32), (5, 8, 33), (5, 8, 65),        # ... four a group, and past that
+])
+def test_merge_of_one_unit_in_pieces(d, slab, T, G, slabs, layout):
+    # one unit of fewer slabs than workgroups: a piece per slab, the last one with 5 keys
+    n = (slabs - 1) * slab + 5
+    q, k, v = _inputs(1, T, G, 1, d, (n + 7) // 8 * 8, seed=7 * slabs + G)
+    for _ in range(2):
+        out, lse = _run(q, k, v, [n], layout)
+    _check(q, k, v, [n], out, lse)
