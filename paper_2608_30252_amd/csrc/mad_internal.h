@@ -96,7 +96,7 @@ struct StreamArgs {
     float scale_log2;
     int cap, Hq, Hkv, G, T, kind;
     int n_wg, base, rem;      // workgroup w runs base (+ 1 for w < rem) consecutive slabs
-    int by_unit;              // 1: instead, the workgroups of a row's units split each unit evenly
+    int by_unit;              // 1, 2: instead, the workgroups of a row's units split each unit evenly (1: the units in turn)
     int B, merge2;            // merge2: the pieces are merged by a second launch
     int rows, wgs;            // slabs, and by_unit workgroups, of one KV head over all rows
     // per row: keys, -, workgroups (by_unit) and slabs of the rows before it (one KV head); past the last row: the end

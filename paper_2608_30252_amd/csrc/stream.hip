@@ -235,12 +235,20 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
     const int T = DRAFT ? 1 : a.T, G = a.G, R = T * G, Hkv = a.Hkv;
 
     // ---- this workgroup's run of slabs: the first one's unit (b, c) and slab t, and their number ----
-    int b, c, t, left;
+    int b, c, t, left, piece = w;   // piece: this run's number within its unit's pieces, less the unit's
     if (a.by_unit) {
         b = __popcll(__ballot(Hkv * a.rec.z <= w)) - 1;   // records past the last row hold the end
         const int k = a.splits(b), rel = w - Hkv * a.wg0(b), n0 = a.slabs(b);
-        c = rel / k;
-        const int part = rel - c * k, lo = n0 / k, hi = n0 - lo * k;   // hi pieces of lo + 1 slabs, then of lo
+        int part;
+        if (a.by_unit == 1) {   // neighbouring workgroups take the row's units in turn (see plan_stream)
+            part = rel / Hkv;
+            c = rel - part * Hkv;
+            piece = w - rel + c * k + part;
+        } else {
+            c = rel / k;
+            part = rel - c * k;
+        }
+        const int lo = n0 / k, hi = n0 - lo * k;   // hi pieces of lo + 1 slabs, then of lo
         t = part * lo + min(part, hi);
         left = lo + (part < hi ? 1 : 0);
     } else {
@@ -570,8 +578,8 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
                     *reinterpret_cast<uint2 *>(bits_ptr<bf16_t>(a.out) + head * D + ps * DP + ch * 4) = pk;
                     if (lse && ps == 0 && ch == 0) lse[head] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
                 } else {
-                    // workgroups and units both advance in slab order, so w + u numbers the pieces one after the other
-                    float *pp = bits_ptr<float>(a.part) + (size_t)(w + u) * piece_floats(R, D);
+                    // runs and units both advance in slab order, so piece + u numbers the pieces one after the other
+                    float *pp = bits_ptr<float>(a.part) + (size_t)(piece + u) * piece_floats(R, D);
                     store_agent4(pp + r * D + ps * DP + ch * 4, y);
                     if (ps == 0 && ch == 0) store_agent2(pp + R * D + 2 * r, M, L);
                 }
@@ -735,12 +743,22 @@ __global__ __launch_bounds__(256) void stream_merge_kernel(const StreamArgs args
 
 // ------------------------------------------------------------------ host ----
 
+constexpr int kInTurnSlabs = 16;   // by-unit runs up to this many slabs: see plan_stream
+
 // One workgroup per CU (its ring fills most of the LDS); fewer when there are
 // fewer slabs.  Two ways to deal the slabs, by the longest share they give:
 //   by unit   unit (b, c) is cut into k_b even pieces, k_b as the row's length
 //             asks: no workgroup crosses a unit, every unit has few pieces;
 //   runs      equal contiguous runs over all units in unit order, for ragged
 //             batches whose pieces would come out uneven.
+// Where a by-unit run of a verify call is at most kInTurnSlabs slabs, neighbouring
+// workgroups take the row's units in turn, so that with 8 KV heads a unit's pieces
+// (its query rows, its partials) stay on one XCD: latency counts there (64/8 heads,
+// d 128, 1 sequence: 2000 keys 11.1 -> 9.8 us, 8000 keys 15.4 -> 14.9; 32/8 heads, 4088
+// keys 10.9 -> 10.3).  Longer runs are bound by HBM, where the pieces of one unit
+// side by side do better (32773 keys: 64/8 heads, runs of 17, 30.3 us against 31.0
+// in turn; 4 sequences, runs of 65, 83.6 against 90), and so do the draft's small
+// ones (4 sequences of 3000 keys, d 128: 14.7 against 15.2).
 // A run that crosses into the next unit stalls once (the flush, 1.6 us at 48
 // rows, d 128) and units get one piece more, so by unit is taken up to 2 slabs
 // and 1/16 above the even share: the draft's 16 sequences of 700 .. 1500 keys
@@ -783,7 +801,7 @@ void plan_stream(StreamArgs &a, int B, int Hkv, int d, const int *n_keys) {
         }
         if (!whole && wgs * Hkv > kStreamWGs) continue;
         for (int b = B; b < kMaxB; ++b) a.row[b].z = wgs;
-        a.by_unit = 1;
+        a.by_unit = a.kind != kStreamDraft && share <= kInTurnSlabs ? 1 : 2;
         a.wgs = wgs;
         a.n_wg = wgs * Hkv;
         break;
