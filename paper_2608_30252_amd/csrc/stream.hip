@@ -296,9 +296,18 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
     for (int j = 0; j < LPW; ++j) {
         const int cidx = (wave * LPW + j) * 64 + lane, kr = cidx / C::CPR, slot = cidx % C::CPR;
         k_off[j] = kr * C::RB + ((slot ^ k_swz<D>(kr)) << 4) - 1024 * j;
-        v_off[j] = kr * C::RB + ((slot ^ v_swz<D>(kr)) << 4) - 1024 * j;
+        if constexpr (VNAT) {
+            v_off[j] = kr * C::RB + ((slot ^ v_swz<D>(kr)) << 4) - 1024 * j;
+        } else {   // V^T: a run of SLAB keys of feature cidx / VCH (from j = 1 on at least 1024 bytes on: cap >= SLAB where used)
+            const int f = cidx / C::VCH, vs = cidx % C::VCH;
+            v_off[j] = (uint32_t)f * (uint32_t)a.cap * 2 + ((vs ^ (f & 7)) << 4) - 1024 * j;
+        }
     }
     static_assert(LPW == 2, "lds_stream16_x2");
+    // Every byte is read once, hence the non-temporal hint, but for V^T runs that are not whole 128-byte
+    // lines: the next slab's run takes the rest of this one's lines from L2 (8 KV heads, d 128, 32773 keys, 4
+    // sequences, cap 32776: 110 -> 89 us; with whole lines, cap 32832, 86.4 us cached and 84.2 so).
+    const bool v_nt = VNAT || a.cap % 64 == 0;
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(smem)) + wv * LPW * 1024;
     // the first slab of a unit (or of the run) needs a free query area
     auto can_issue = [&]() {
@@ -317,8 +326,8 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
         }
         // a slab whose rows all exist in one place (draft: in the memory, or in the ring without a
         // wrap) has one base and fixed lane offsets
-        const bf16_t *k0 = i_k, *v0 = i_v;
-        bool one = VNAT && i_keys >= C::SLAB;
+        const bf16_t *k0 = i_k, *v0 = VNAT ? i_v : i_v + (int64_t)i_t * C::SLAB;
+        bool one = i_keys >= C::SLAB && (VNAT || a.cap <= (int)(0xffffffffu / (2 * D)));   // (32-bit lane offsets)
         if constexpr (DRAFT) {
             const int kb = i_t * C::SLAB;
             one = kb + C::SLAB <= i_mlen;
@@ -332,7 +341,8 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
         }
         if (one) {
             lds_stream16_x2<true>(k0, k_off[0], k_off[1], lds0 + i_stage);
-            lds_stream16_x2<true>(v0, v_off[0], v_off[1], lds0 + i_stage + C::KBYTES);
+            if (v_nt) lds_stream16_x2<true>(v0, v_off[0], v_off[1], lds0 + i_stage + C::KBYTES);
+            else lds_stream16_x2<false>(v0, v_off[0], v_off[1], lds0 + i_stage + C::KBYTES);
         } else if constexpr (DRAFT) {
             // row by row: memory, ring, the new token; rows past the end repeat the last one (masked),
             // those of an empty row read the queries (never used)
@@ -446,6 +456,16 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
                 const int f = db * 16 + lr;
                 vf[db] = *reinterpret_cast<const bf16x8_v *>(sv8 + f * C::VROW + (((4 * kh + lg) ^ (f & 7)) << 4));
             }
+            if (kb + C::SLAB > len) {   // the unit's last slab: values of keys past len may be anything, zero them
+                u32x4_v keep;
+                #pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int kk = kb + 32 * kh + 8 * lg + 2 * e;
+                    keep[e] = kk >= len ? 0u : kk + 1 >= len ? 0x0000ffffu : 0xffffffffu;
+                }
+                #pragma unroll
+                for (int db = 0; db < DB; ++db) vf[db] = __builtin_bit_cast(bf16x8_v, __builtin_bit_cast(u32x4_v, vf[db]) & keep);
+            }
         }
         f32x4_v sacc[2];
         #pragma unroll
@@ -493,21 +513,7 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
             for (int db = 0; db < DB; ++db) o[db] *= alpha;
         }
         #pragma unroll
-        for (int db = 0; db < DB; ++db) {
-            if constexpr (!VNAT) {
-                if (kg0 + 8 > len) {   // values of keys past len may be anything: zero them
-                    u32x4_v x = __builtin_bit_cast(u32x4_v, vf[db]);
-                    #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int kk = kg0 + 2 * e;
-                        if (kk >= len) x[e] = 0u;
-                        else if (kk + 1 >= len) x[e] &= 0x0000ffffu;
-                    }
-                    vf[db] = __builtin_bit_cast(bf16x8_v, x);
-                }
-            }
-            o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[db], pf, o[db], 0, 0, 0);
-        }
+        for (int db = 0; db < DB; ++db) o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[db], pf, o[db], 0, 0, 0);
     };
 
     // ---- end of a unit's run in this workgroup: the key groups' results go to

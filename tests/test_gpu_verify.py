@@ -221,3 +221,21 @@ def test_merge_of_one_unit_in_pieces(d, slab, T, G, slabs, layout):
     for _ in range(2):
         out, lse = _run(q, k, v, [n], layout)
     _check(q, k, v, [n], out, lse)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("tail", [0, 1, 5, 63, 64])
+@pytest.mark.parametrize("pad", [0, 8, 32])
+def test_transposed_v_runs_off_line_boundaries(d, tail, pad):
+    # V^T runs that are whole 128-byte lines (cap a multiple of 64) or not; full slabs and a last one of `tail`
+    # keys whose values past len are not finite
+    n = 3 * 128 + tail
+    cap = (n + 63) // 64 * 64 + pad
+    q, k, v = _inputs(2, 3, 8, 2, d, cap, seed=31 + tail + pad)
+    length = [n, n - 128]
+    kn, vn = k.clone(), v.clone()
+    for b in range(2):
+        kn[b, :, length[b]:] = float("nan")
+        vn[b, :, length[b]:] = float("nan")
+    out, lse = _run(q, kn, vn, length, "transposed_v")
+    _check(q, k, v, length, out, lse)
