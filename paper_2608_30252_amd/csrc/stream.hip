@@ -240,7 +240,7 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
         b = __popcll(__ballot(Hkv * a.rec.z <= w)) - 1;   // records past the last row hold the end
         const int k = a.splits(b), rel = w - Hkv * a.wg0(b), n0 = a.slabs(b);
         int part;
-        if (a.by_unit == 1) {   // neighbouring workgroups take the row's units in turn (see plan_stream)
+        if (!DRAFT && a.by_unit == 1) {   // neighbouring workgroups take the row's units in turn (see plan_stream)
             part = rel / Hkv;
             c = rel - part * Hkv;
             piece = w - rel + c * k + part;
