@@ -686,14 +686,23 @@ static int decode_nsub(int units, int n_max, int G, int d, int dtype) {
 // matrix-core products (stream_kernel) instead of the split kernel above, which
 // starts and ends sooner (6.0 us against 8.5 for one sequence of 2000 keys, 8
 // KV heads, d 64) and does as well on even batches at head_dim 64.  bf16 only.
-// Measured (split -> stream, us; Hkv 8 unless given):
+// Measured over 1 .. 64 sequences, 2 and 8 KV heads, 1 .. 256 slabs a unit, lengths
+// even, 0.6 .. 1 and 0.2 .. 1 of the longest (split -> stream, us; Hkv 8 unless given):
 //   G 16: the vector-ALU products bound the split kernel (2 KV heads, 2000 keys:
-//     12.3 -> 9.2 at d 64, 22.5 -> 11.5 at d 128), from a few slabs on;
-//   G 8 or d 128: long launches (G 4, d 128: 8000 keys 15.1 -> 14.1, 32768 keys
-//     42.8 -> 29.0, 16 of 500 .. 3000 keys 40.5 -> 28.9; 4000 keys in all 9.8 -> 10.2);
-//   G <= 4, d 64: ragged batches with units long enough to carry a flush each
-//     (64 of 600 .. 3200 keys 56 -> 50, 16 of 500 .. 3000 19.5 -> 17.7; but 64 of
-//     100 .. 800 18.6 -> 24.3, and 16 of 1500 each 13.3 -> 14.1).
+//     12.3 -> 8.4 at d 64, 33.9 -> 9.7 for 3000 at d 128).  At d 128 a few units of 2 .. 4
+//     slabs are the exception (8 sequences of 188 keys, 2 KV heads: 8.9 -> 9.35);
+//   G 8, d 64: from 512 slabs (16 of 500 keys 12.0 -> 9.65), units of one slab
+//     excepted (64 of 90 keys 8.5 -> 8.9);
+//   d 128: long launches (G 4: 32768 keys 42.8 -> 27.0, 4 of 3000 16.3 -> 14.7, 16 of
+//     500 .. 3000 29.0 -> 25.2) whose units carry a flush each: with two or more units to a
+//     workgroup, 64 of 120 keys 11.7 -> 12.7, 64 of 50 .. 256 17.1 -> 21.2, but 64 of
+//     148 .. 778 37.4 -> 34.5 and, whole units, 64 of 256 each 18.4 -> 17.5.  Few query heads stream later: G 1 only
+//     from 4096 slabs (64 of 1024 keys 46.8 -> 44.9; but 8200 keys 13.2 -> 13.8) or ragged
+//     (16 of 400 .. 2048 keys 24.5 -> 22.8);
+//   G <= 4, d 64: ragged batches of long units (G 4: 64 of 600 .. 3200 keys 56 -> 50,
+//     16 of 500 .. 3000 20.4 -> 18.0; but 64 of 100 .. 800 18.6 -> 24.3) and, from two query
+//     heads per KV head on, the longest launches (G 4: 64 of 2000 keys 43.6 -> 42.3, of 3000
+//     63.5 -> 61.2; G 1: 64 of 2200 keys 45.0 -> 45.9).
 bool decode_streams(int B, int Hkv, int G, int d, int dtype, const int *n_keys) {
     if (dtype != MAD_BF16) return false;
     const int slab = stream_slab(d);
@@ -703,10 +712,20 @@ bool decode_streams(int B, int Hkv, int G, int d, int dtype, const int *n_keys) 
         keys += n_keys[b];
         most = n_keys[b] > most ? n_keys[b] : most;
     }
+    const int64_t units = (int64_t)B * Hkv;
+    const bool even = most > 0 && slabs == ((most - 1) / slab + 1) * B;   // units of one number of slabs
+    const bool ragged = keys * 10 <= most * B * 7;
     slabs *= Hkv;
-    if (G == 16) return slabs >= 32;
-    if (G == 8 || d == 128) return slabs >= (d == 128 ? 1024 : 512);
-    return slabs >= (int64_t)8 * B * Hkv && (slabs >= 8192 || (slabs >= 1024 && keys * 10 <= most * B * 7));
+    if (G == 16) return slabs >= 32 && (d == 64 || slabs == units || slabs >= 5 * units || slabs >= 256);
+    if (d == 64) {
+        if (G == 8) return slabs >= 512 && slabs > units;
+        if (G == 1) return ragged && slabs >= 1024 && slabs >= 64 * units;
+        return slabs >= (G == 4 ? 8 : 16) * units && (slabs >= 8192 || (slabs >= 1024 && ragged));
+    }
+    if (G == 1)
+        return (slabs >= 4096 && slabs >= 8 * units) ||
+               (ragged && slabs >= 10 * units && (slabs >= 2048 || (slabs >= 1024 && slabs >= 32 * units)));
+    return slabs >= (G == 2 ? 1100 : 1024) && keys >= (even ? (G == 2 ? 6 : 4) : G == 8 ? 5 : G == 4 ? 7 : 8) * (int64_t)slab * B;
 }
 
 DecodePlan plan_decode(int B, int Hkv, int G, int d, int dtype, const int *n_keys) {
