@@ -1,9 +1,10 @@
 """The native marshalling of the binding against the ctypes path.
 
-A call whose lengths and positions come as numpy arrays is not the ordinary one
-and takes the ctypes path; the same values in lists take the native one.  Both
-must pass the same arguments on, so every output is bit-identical; and a failed
-check or a return code of the library raises the same error on both.
+The same calls are made through the native functions and with the ctypes path
+alone.  Both must pass the same arguments on, so every output is bit-identical;
+a failed check or a return code of the library raises the same error on both.
+What the native functions return says which path served a call: the library's
+code, or None where they hand it on (lengths and positions in numpy arrays).
 """
 import contextlib
 import ctypes
@@ -41,17 +42,76 @@ def _calls(mad, as_seq):
     xr, gm, wq = n((2, D), 13), n((D,), 14), n(((Hq + 2 * Hkv) * d, D), 15, 0.02)
     qo, ko, vo, xn = (torch.empty(s, dtype=torch.bfloat16, device=dev) for s in ((2, Hq, d), (2, Hkv, d), (2, Hkv, d), (2, D)))
     yield "qkv", [qo, ko, vo, xn], lambda: mad.rmsnorm_qkv_rope(xr, gm, wq, as_seq([5, 70]), Hq, Hkv, d, qo, ko, vo, xn)
+    # (no host sequence in these)
+    wo, res, lo = n((256, D), 16, 0.02), n((2, 256), 17), torch.empty(2, 256, dtype=torch.bfloat16, device=dev)
+    yield "linear", [lo], lambda: mad.linear_residual(xr, wo, res, lo)
+    wg, so = n((2 * 4096, D), 18, 0.02), torch.empty(2, 4096, dtype=torch.bfloat16, device=dev)
+    yield "swiglu", [so], lambda: mad.rmsnorm_swiglu(xr, gm, wg, so)
+    V = 5000
+    for rows in (1, 4):
+        draft = torch.randint(0, V, (B, rows - 1), dtype=torch.int32, device=dev, generator=torch.Generator(dev).manual_seed(19)) if rows > 1 else None
+        for dt in (torch.float32, torch.bfloat16):
+            lg, na, nt = n((B, rows, V), 20, dt=dt), *(torch.empty(B, dtype=torch.int32, device=dev) for _ in range(2))
+            yield "greedy", [na, nt], lambda: mad.accept_greedy(lg, draft, na, nt)
+    pp, pq = (torch.softmax(n((B, r, V), 21 + r, dt=torch.float32), -1) for r in (4, 3))
+    u = torch.rand(B, 4, device=dev, generator=torch.Generator(dev).manual_seed(22))
+    sa, st = (torch.empty(B, dtype=torch.int32, device=dev) for _ in range(2))
+    yield "stoch", [sa, st], lambda: mad.accept_stochastic(pp, pq, draft, u, sa, st)
 
 
-def test_native_and_ctypes_marshalling_agree():
+class _Recorded:
+    """The native module, and what its functions returned."""
+
+    def __init__(self, fast):
+        self.fast, self.returned = fast, []
+
+    def __getattr__(self, name):
+        def call(*args):
+            self.returned.append((name, getattr(self.fast, name)(*args)))
+            return self.returned[-1][1]
+        return call
+
+
+def test_native_and_ctypes_marshalling_agree(monkeypatch):
     import paper_2608_30252_amd as mad
-    for (name, a, f), (_, b, g) in zip(_calls(mad, list), _calls(mad, np.array)):
-        for call in (f, g, f, g):   # the first native call finds no workspace yet and leaves it to the ctypes path
+    native, ctypes_only = _Recorded(mad._fast()), mad._CtypesOnly()
+    served = set()
+    for (name, a, f), (_, b, g), (_, _, h) in zip(_calls(mad, list), _calls(mad, list), _calls(mad, np.array)):
+        for call, fast in ((f, native), (g, ctypes_only), (f, native), (g, ctypes_only)):
+            monkeypatch.setattr(mad, "_FAST", fast)   # the first native call may find no workspace yet
             call()
         torch.cuda.synchronize()
+        function, rc = native.returned[-1]
+        assert rc == mad.MAD_OK, f"{name}: {function} returned {rc}"   # served natively, not handed on (None)
+        served.add(function)
         for i, (s, t) in enumerate(zip(a, b)):
             bits = torch.int16 if s.dtype == torch.bfloat16 else torch.int32
             assert torch.equal(s.view(bits), t.view(bits)), f"{name}: output {i}"
+        if name in ("decode", "step", "update", "verify", "verify_vt", "qkv"):   # lengths in arrays are handed on
+            monkeypatch.setattr(mad, "_FAST", native)
+            h()
+            assert native.returned[-1] == (function, None), name
+    assert served == {"attn", "update", "verify", "verify_vt", "greedy", "stoch", "qkv", "linear", "swiglu"}
+
+
+def test_a_side_stream_has_its_own_workspace(monkeypatch):
+    import paper_2608_30252_amd as mad
+    native = _Recorded(mad._fast())
+    name, (out, lse, *_), f = next(_calls(mad, list))
+    f()
+    torch.cuda.synchronize()
+    want = out.clone(), lse.clone()
+    out.zero_()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        f()   # allocates the stream's workspace through the ctypes path
+        monkeypatch.setattr(mad, "_FAST", native)
+        f()
+        side.synchronize()
+        keys = [k for k in mad._default_ws if k[1] == side.cuda_stream]
+    assert native.returned == [("attn", mad.MAD_OK)] and len(keys) == 1
+    assert torch.equal(out.view(torch.int16), want[0].view(torch.int16)) and torch.equal(lse, want[1])
 
 
 @pytest.mark.parametrize("as_seq", [list, np.array])

@@ -16,13 +16,14 @@ import pytest
 import torch
 
 from parity import abs_score_batched, check_lse, check_out, to_np
+from test_decode_route import BF16, streams
 
 pytestmark = pytest.mark.gpu
 
 BASE = 500000.0
 
 
-def _fused_boundary(dtype, Hq, Hkv, d, S, W, r, u, prefix, seed):
+def _fused_boundary(dtype, Hq, Hkv, d, S, W, r, u, prefix, seed, stream=False):
     import oracle
     from oracle.masw_sets import MaswSets
     import paper_2608_30252_amd as mad
@@ -82,6 +83,9 @@ def _fused_boundary(dtype, Hq, Hkv, d, S, W, r, u, prefix, seed):
     views, modes = lay.step_views(p)
     R = len(views)
     assert R == 1 + n_new and modes[0] == 2 and modes.count(1) == 1
+    if bf:
+        lens = [v.mem_len + v.win_len + (1 if m else 0) for v, m in zip(views, modes)]
+        assert streams(lens, Hkv, Hq // Hkv, d, BF16) == stream
     q = synth.normal((R, Hq, d), 5_000_000 * seed + p, dtype=dtype)
     kn = torch.stack([k_new] * R)
     vn = torch.stack([v_new] * R)
@@ -121,3 +125,14 @@ def test_fused_boundary_paper_setting_fp32():
 
 def test_fused_boundary_per_boundary_schedule_bf16():
     _fused_boundary(torch.bfloat16, 16, 8, 128, S=0, W=512, r=16, u=1, prefix=8192 + 3, seed=3)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,W,prefix", [
+    (32, 2, 64, 512, 3000),      # 16 query heads per KV head: a few slabs a row already stream
+    (32, 2, 128, 512, 3000),
+    (32, 8, 128, 1024, 16384),   # a long launch, units in many pieces
+])
+def test_fused_boundary_on_the_stream_kernel(Hq, Hkv, d, W, prefix):
+    # rows of all three modes alias one memory and one wrapped ring (seq_stride 0); the last slab holds the
+    # new token of the rows that attend it, and one row appends it
+    _fused_boundary(torch.bfloat16, Hq, Hkv, d, S=0, W=W, r=16, u=4, prefix=prefix, seed=4 + d, stream=True)

@@ -193,7 +193,9 @@ def test_peaky_queries_full_size(B, Hq, c):
     (5, 3, 24, 6, 128, 3, 700),        # 9 query rows; units of 1 .. 11 slabs, several to a workgroup or one over several
     (33, 6, 64, 8, 64, 6, 1500),       # 48 query rows at d 64 (two key groups of 64 keys), whole units and pieces mixed
     (64, 1, 128, 128, 64, 1, 16),      # 8192 units, more than the arrival counters: a workgroup per unit
-    (1, 8, 8, 1, 64, 40000, 40000),    # one unit over every workgroup: 256 pieces
+    (1, 8, 8, 1, 64, 40000, 40000),    # one unit of 313 slabs: 157 pieces, the last of one slab
+    (1, 8, 8, 1, 64, 32768, 32768),    # one unit over every workgroup: 256 pieces
+    (1, 8, 8, 1, 128, 16384, 16384),
 ])
 def test_runs_of_slabs_over_ragged_units(B, T, Hq, Hkv, d, lo, hi, layout):
     cap = (hi + 7) // 8 * 8

@@ -12,13 +12,14 @@ import pytest
 import torch
 
 from parity import abs_score_batched, check_lse, check_out, to_np
+from test_decode_route import BF16, streams
 
 pytestmark = pytest.mark.gpu
 
 
-def _inputs(B, mlen, wlen, wcap, seed):
+def _inputs(B, mlen, wlen, wcap, seed, Hkv=8):
     from paper_2608_30252_amd import synth
-    Hq, Hkv, d = 32, 8, 64
+    Hq, d = 32, 64
     s = 1000 * seed
     g = dict(q=synth.normal((B, Hq, d), s + 1), mk=synth.normal((B, Hkv, mlen, d), s + 2),
              mv=synth.normal((B, Hkv, mlen, d), s + 3), wk=synth.normal((B, Hkv, wcap, d), s + 4),
@@ -40,13 +41,15 @@ def _oracle(g, B, mlen, wlen, wstart, wcap):
     return o, lse, abs_score_batched(g["q"].double().numpy(), K, n, d ** -0.5)
 
 
-def test_noalloc_matches_workspace_entry_point_on_two_calls():
+@pytest.mark.parametrize("Hkv", [8, 2])   # split kernel; with 16 query heads per KV head the stream kernel
+def test_noalloc_matches_workspace_entry_point_on_two_calls(Hkv):
     import paper_2608_30252_amd as mad
     dev = torch.device("cuda")
     lib = mad._load_library()
     # 4 sequences of the 32K compact layer (2048 slots + 1023 window + new), then 1 sequence of 700 keys
     for case, (B, mlen, wlen, wcap) in enumerate([(4, 2048, 1023, 1056), (1, 500, 199, 256)]):
-        g = _inputs(B, mlen, wlen, wcap, seed=70 + case)
+        g = _inputs(B, mlen, wlen, wcap, seed=70 + case, Hkv=Hkv)
+        assert streams([mlen + wlen + 1] * B, Hkv, 32 // Hkv, 64, BF16) == (Hkv == 2 and case == 0)
         wstart = [(37 * b + 11 * case) % wcap for b in range(B)]
         d = g["q"].shape[-1]
         results = []
@@ -57,12 +60,12 @@ def test_noalloc_matches_workspace_entry_point_on_two_calls():
             out = torch.full_like(t["q"], float("nan"))
             lse = torch.full((B, t["q"].shape[1]), float("nan"), device=dev)
             if entry == "workspace":
-                ws = torch.zeros(mad.workspace_bytes(mad.MAD_OP_DECODE, B, 32, 8, d), dtype=torch.uint8, device=dev)
+                ws = torch.zeros(mad.workspace_bytes(mad.MAD_OP_DECODE, B, 32, Hkv, d), dtype=torch.uint8, device=dev)
                 mad.draft_decode_attn(t["q"], mem, win, t["kn"], t["vn"], out, lse, ws=ws)
             else:   # straight through the C ABI
                 mv, wv = mem.view(B), win.view(B)
                 rc = lib.mad_draft_decode_attn_noalloc(
-                    ctypes.c_void_p(t["q"].data_ptr()), B, 32, 8, d, mad.MAD_BF16, ctypes.c_float(d ** -0.5),
+                    ctypes.c_void_p(t["q"].data_ptr()), B, 32, Hkv, d, mad.MAD_BF16, ctypes.c_float(d ** -0.5),
                     ctypes.byref(mv), ctypes.byref(wv), ctypes.c_void_p(t["kn"].data_ptr()),
                     ctypes.c_void_p(t["vn"].data_ptr()), ctypes.c_void_p(out.data_ptr()),
                     ctypes.c_void_p(lse.data_ptr()), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
