@@ -42,8 +42,9 @@
 // conversions, and nothing else of weight: no maxima (a fifth of the vector work
 // before), no address arithmetic (stage and half are instruction offsets), no
 // staging registers (128 registers: four waves per SIMD instead of three).
-// 32K prefix, 32/8 heads, 2048 slots: 792 -> 612 us; 4 ragged prefixes at d 128,
-// W 128: 492 -> 404 us (two waves per SIMD there: latency-bound).  Measured
+// 32K prefix, 32/8 heads, 2048 slots: 785 -> 627 us; 4 ragged prefixes at d 128,
+// W 128: 492 -> 406 us (two waves per SIMD there: latency-bound); one of 330
+// tokens at d 128: 18.1 -> 16.2.  Measured
 // and not kept: 64 rows per wave (685 us against 703 on long windows, but twice the time
 // with one query head per KV head), 32-key tiles in three stages at d 128 (419 - 426).
 // Query blocks of every unit are dealt round-robin over the units (with a

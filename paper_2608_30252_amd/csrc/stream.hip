@@ -14,8 +14,9 @@
 // splits per unit, sized by the longest sequence, 16 sequences of 600 .. 12000
 // keys ran at 3.5 TB/s.  A run covers whole units, the tail of its first unit
 // and the head of its last; whole units are finished by their workgroup,
-// pieces of a unit are merged by the last workgroup to arrive at it (one
-// arrival counter per unit), so a call is a single launch.
+// small pieces of a unit are merged by the last workgroup to arrive at it (one
+// arrival counter per unit), so such a call is a single launch; where a unit
+// has many or large pieces a second launch merges them (plan_stream).
 //
 // Both products run on the matrix cores (v_mfma_f32_16x16x32_bf16, fp32
 // accumulation):
@@ -46,7 +47,8 @@
 
 namespace mad {
 
-// phase marks of the diagnostic trace build: 0 entry, 1 the run's last slab done
+// phase marks of the diagnostic trace build: 0 entry, 1 the run's last slab done and,
+// where the launch merges, 2 its pieces acknowledged, 3 the arrivals known, 4 merged
 MAD_TRACE_BUFFER(mad_trace_verify)
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_v;
