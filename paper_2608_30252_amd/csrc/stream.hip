@@ -309,7 +309,7 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
     // Every byte is read once, hence the non-temporal hint, but for V^T runs that are not whole 128-byte
     // lines: the next slab's run takes the rest of this one's lines from L2 (8 KV heads, d 128, 32773 keys, 4
     // sequences, cap 32776: 110 -> 89 us; with whole lines, cap 32832, 86.4 us cached and 84.2 so).
-    const bool v_nt = VNAT || a.cap % 64 == 0;
+    const bool v_nt = VNAT || (((a.cap | a.head | a.seq) % 64 == 0) && a.v % 128 == 0);
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(smem)) + wv * LPW * 1024;
     // the first slab of a unit (or of the run) needs a free query area
     auto can_issue = [&]() {
