@@ -80,7 +80,8 @@ bool update_uses_gemv(int R, int D, int dtype);
 constexpr int kStreamWGs = 256;   // workgroups of a launch: one per CU
 __host__ __device__ constexpr int stream_slab(int d) { return d == 128 ? 64 : 128; }   // keys per slab (32 KB of K + V)
 
-constexpr int kMergeInLaunch = 48 << 10;   // bytes of a unit's pieces that a workgroup of the launch itself merges (plan_stream)
+constexpr int kMergeBytes = 128 << 10;      // LDS for the pieces of a unit that a workgroup merges in the launch
+constexpr int kMergeInLaunch = 48 << 10;    // such pieces where the units are few (plan_stream)
 
 // verify over a cache of K and V rows; over K rows and V^T (one run of cap keys per feature);
 // the draft's decode: memory rows, window ring, new token (T = 1)

@@ -656,20 +656,29 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
     const int last = (s_last[0] ? 1 : 0) + (s_last[1] ? 2 : 0);
     if (last == 0) return;
     const int bytes0 = (last & 1) ? up0.np * pf * 4 : 0, bytes1 = (last & 2) ? up1.np * pf * 4 : 0;
-    const int at1 = (bytes0 + 1023) & ~1023;   // both fit: plan_stream gives units of more than kMergeInLaunch a second launch
-    static_assert(2 * kMergeInLaunch + 1024 <= C::OFF_Q, "two units' pieces fit the ring");
+    const int at1 = (bytes0 + 1023) & ~1023;
+    static_assert(kMergeBytes <= C::OFF_Q, "the pieces lie in the ring");
     __shared__ float sinv[2 * MAD_MAX_VERIFY_ROWS];
-    if (last & 1) load_pieces(part + (size_t)up0.p0 * pf, bytes0, smem);
-    if (last & 2) load_pieces(part + (size_t)up1.p0 * pf, bytes1, smem + at1);
-    const MergeJob<D> j0 = {pu0, up0.np, R, smem, smem + R * D * 4, pf * 4, sinv};
-    const MergeJob<D> j1 = {pu1, up1.np, R, smem + at1, smem + at1 + R * D * 4, pf * 4, sinv + R};
-    wait_vm(0);
-    __syncthreads();
-    if (last & 1) j0.weights(a);
-    if (last & 2) j1.weights(a);
-    __syncthreads();
-    if (last & 1) j0.sums(a);
-    if (last & 2) j1.sums(a);
+    auto merge = [&](bool first_unit, bool second_unit, int at) {
+        if (first_unit) load_pieces(part + (size_t)up0.p0 * pf, bytes0, smem);
+        if (second_unit) load_pieces(part + (size_t)up1.p0 * pf, bytes1, smem + at);
+        const MergeJob<D> j0 = {pu0, up0.np, R, smem, smem + R * D * 4, pf * 4, sinv};
+        const MergeJob<D> j1 = {pu1, up1.np, R, smem + at, smem + at + R * D * 4, pf * 4, sinv + R};
+        wait_vm(0);
+        __syncthreads();
+        if (first_unit) j0.weights(a);
+        if (second_unit) j1.weights(a);
+        __syncthreads();
+        if (first_unit) j0.sums(a);
+        if (second_unit) j1.sums(a);
+    };
+    if (at1 + bytes1 <= kMergeBytes) {
+        merge(last & 1, last & 2, at1);
+    } else {   // one after the other (each fits: plan_stream)
+        merge(true, false, 0);
+        __syncthreads();
+        merge(false, true, 0);
+    }
     MAD_TRACE(mad_trace_verify, 4);
 }
 
@@ -818,14 +827,20 @@ void plan_stream(StreamArgs &a, int B, int Hkv, int d, const int *n_keys) {
         np_max = (nt_max - 1) / a.base + 2;
         np_max = np_max > a.n_wg ? a.n_wg : np_max;
     }
-    // A unit's pieces up to kMergeInLaunch are merged by the last workgroup at it; larger ones by a second
-    // launch, which costs 2 - 3 us but spreads over the CUs what one workgroup does serially (32/8 heads, d 128,
-    // 5 queries, 1 sequence: 1000 keys, 16 pieces of 10 KB, 13.4 -> 8.4 us; 4100 keys, 22 pieces, 17.9 -> 11.4;
-    // 32773 keys, 32 pieces, 29.5 -> 26.9).  Either side of the line: 4 pieces, 42 KB, of 8 sequences of 2000
-    // keys 18.4 us in the launch, 18.7 in two; 32 pieces of 4 rows, 64 KB, of a decode of 32768 keys at d 128
-    // 28.1 and 26.8.
+    // A unit's pieces are merged by the last workgroup at it, or by a second launch, which takes 1 - 2 us of the
+    // host's time and of the GPU's, more with many units, but spreads over the CUs what one workgroup does serially.  Calls issued one
+    // by one / in a graph replay (us; 32/8 heads, d 128, 5 queries unless given), in the launch -> in two:
+    //   up to 48 KB of pieces: 256 keys, 42 KB, 8.6 -> 9.4 / 9.5 -> 8.6; 2000 keys T 1 G 1, 32 pieces of one row,
+    //     8.6 -> 9.5 / 9.65 -> 8.6 (a longer chain in the launch, but the host has one to issue);
+    //   above: 1000 keys, 166 KB, 13.4 -> 8.2 in a graph; 4100 keys 17.9 -> 11.2; 32773 keys 29.5 -> 26.9; 4 of 512
+    //     keys, 83 KB, 10.5 -> 8.8 / 11.7 -> 9.4;
+    //   many units, up to the LDS: 64 sequences of 512 keys, 32/2 heads, T 4, 2 pieces of 33 KB, 17.2 -> 22.5 /
+    //     18.4 -> 23.4; 16 of 512 keys at d 64, 4 of 17 KB, 9.7 -> 11.4 / 10.5 -> 11.0.
     const int64_t bytes = (int64_t)np_max * piece_floats(a.T * a.G, d) * 4;
-    a.merge2 = bytes > kMergeInLaunch ? 1 : 0;
+    const int units = B * Hkv;
+    const bool in_launch = bytes <= kMergeInLaunch || (units >= 64 && bytes <= kMergeBytes) ||
+                           (units >= 32 && np_max <= 4 && bytes <= 72 << 10);
+    a.merge2 = np_max > 1 && !in_launch ? 1 : 0;
 }
 
 // the pieces of a launch's units: at most one per workgroup and unit

@@ -193,6 +193,8 @@ def test_peaky_queries_full_size(B, Hq, c):
     (5, 3, 24, 6, 128, 3, 700),        # 9 query rows; units of 1 .. 11 slabs, several to a workgroup or one over several
     (33, 6, 64, 8, 64, 6, 1500),       # 48 query rows at d 64 (two key groups of 64 keys), whole units and pieces mixed
     (64, 1, 128, 128, 64, 1, 16),      # 8192 units, more than the arrival counters: a workgroup per unit
+    (60, 4, 64, 4, 128, 64, 520),      # 240 units of 64 rows in runs: the pieces of a workgroup's two units do not fit the LDS together
+    (16, 4, 32, 2, 64, 400, 512),      # 32 units in 4 pieces of 17 KB, merged in the launch
     (1, 8, 8, 1, 64, 40000, 40000),    # one unit of 313 slabs: 157 pieces, the last of one slab
     (1, 8, 8, 1, 64, 32768, 32768),    # one unit over every workgroup: 256 pieces
     (1, 8, 8, 1, 128, 16384, 16384),
@@ -211,8 +213,8 @@ def test_runs_of_slabs_over_ragged_units(B, T, Hq, Hkv, d, lo, hi, layout):
 @pytest.mark.parametrize("layout", LAYOUTS)
 @pytest.mark.parametrize("d,slab", [(64, 128), (128, 64)])
 @pytest.mark.parametrize("T,G,slabs", [
-    (1, 1, 2), (1, 1, 100),                    # pieces of one row, merged in the launch
-    (4, 4, 5), (4, 4, 12),                     # 16 rows: the last sizes in the launch (d 128, d 64) and the first past it
+    (1, 1, 2), (1, 1, 90),                     # pieces of one row, merged in the launch
+    (4, 4, 5), (4, 4, 6), (4, 4, 11), (4, 4, 12),   # 16 rows: the last sizes in the launch (5 at d 128, 11 at d 64) and the first past it
     (5, 8, 8), (5, 8, 9), (5, 8, 16), (5, 8, 17),   # a second launch: one piece a thread group (8 groups at d 128, 16 at d 64), and one more
     (5, 8, 32), (5, 8, 33), (5, 8, 65),        # ... four a group, and past that
 ])
