@@ -241,15 +241,13 @@ __global__ __launch_bounds__(512, 1) void stream_kernel(const StreamArgs args) {
     if (a.by_unit) {
         b = __popcll(__ballot(Hkv * a.rec.z <= w)) - 1;   // records past the last row hold the end
         const int k = a.splits(b), rel = w - Hkv * a.wg0(b), n0 = a.slabs(b);
-        int part;
-        if (!DRAFT && a.by_unit == 1) {   // neighbouring workgroups take the row's units in turn (see plan_stream)
-            part = rel / Hkv;
-            c = rel - part * Hkv;
-            piece = w - rel + c * k + part;
-        } else {
-            c = rel / k;
-            part = rel - c * k;
-        }
+        // by_unit 1: neighbouring workgroups take the row's units in turn (plan_stream); one division for both
+        // orders, since every line of instructions here is a miss in a short launch
+        const bool turn = !DRAFT && a.by_unit == 1;
+        const int m = turn ? Hkv : k, x0 = rel / m, x1 = rel - x0 * m;
+        c = turn ? x1 : x0;
+        const int part = turn ? x0 : x1;
+        if (!DRAFT) piece = w - rel + c * k + part;
         const int lo = n0 / k, hi = n0 - lo * k;   // hi pieces of lo + 1 slabs, then of lo
         t = part * lo + min(part, hi);
         left = lo + (part < hi ? 1 : 0);
@@ -760,22 +758,20 @@ __global__ __launch_bounds__(256) void stream_merge_kernel(const StreamArgs args
 
 // ------------------------------------------------------------------ host ----
 
-constexpr int kInTurnSlabs = 16;   // by-unit runs up to this many slabs: see plan_stream
-
 // One workgroup per CU (its ring fills most of the LDS); fewer when there are
 // fewer slabs.  Two ways to deal the slabs, by the longest share they give:
 //   by unit   unit (b, c) is cut into k_b even pieces, k_b as the row's length
 //             asks: no workgroup crosses a unit, every unit has few pieces;
 //   runs      equal contiguous runs over all units in unit order, for ragged
 //             batches whose pieces would come out uneven.
-// Where a by-unit run of a verify call is at most kInTurnSlabs slabs, neighbouring
-// workgroups take the row's units in turn, so that with 8 KV heads a unit's pieces
-// (its query rows, its partials) stay on one XCD: latency counts there (64/8 heads,
-// d 128, 1 sequence: 2000 keys 11.1 -> 9.8 us, 8000 keys 15.4 -> 14.9; 32/8 heads, 4088
-// keys 10.9 -> 10.3).  Longer runs are bound by HBM, where the pieces of one unit
-// side by side do better (32773 keys: 64/8 heads, runs of 17, 30.3 us against 31.0
-// in turn; 4 sequences, runs of 65, 83.6 against 90), and so do the draft's small
-// ones (4 sequences of 3000 keys, d 128: 14.7 against 15.2).
+// Neighbouring workgroups are on different XCDs.  With a multiple of 8 KV heads,
+// taking the row's units in turn keeps a unit's pieces (its query rows, its
+// partials) on one, which counts where the pieces are large and the runs short:
+// from 32 query rows and up to 16 slabs (64/8 heads, d 128, 5 queries, 1 sequence: 2000 keys
+// 11.1 -> 9.8 us, 8000 keys 15.4 -> 14.9; 4 of 512 keys 11.8 -> 10.8), from 17 rows and up to 3 slabs
+// (32/8 heads, 4088 keys 10.9 -> 10.3, 4100 keys 11.5 -> 11.2).  Elsewhere the pieces of one unit side by
+// side do better (8/8 heads, 4 sequences of 2048 keys 12.8 us against 13.6; 64/8 heads, 32773 keys, runs
+// of 17, 30.3 against 31.0; 32/8, 4 sequences, runs of 65, 83.6 against 90).
 // A run that crosses into the next unit stalls once (the flush, 1.6 us at 48
 // rows, d 128) and units get one piece more, so by unit is taken up to 2 slabs
 // and 1/16 above the even share: the draft's 16 sequences of 700 .. 1500 keys
@@ -818,7 +814,7 @@ void plan_stream(StreamArgs &a, int B, int Hkv, int d, const int *n_keys) {
         }
         if (!whole && wgs * Hkv > kStreamWGs) continue;
         for (int b = B; b < kMaxB; ++b) a.row[b].z = wgs;
-        a.by_unit = a.kind != kStreamDraft && share <= kInTurnSlabs ? 1 : 2;
+        a.by_unit = Hkv % 8 == 0 && share <= (a.T * a.G >= 32 ? 16 : a.T * a.G > 16 ? 3 : 0) ? 1 : 2;
         a.wgs = wgs;
         a.n_wg = wgs * Hkv;
         break;
