@@ -771,7 +771,9 @@ __global__ __launch_bounds__(256) void stream_merge_kernel(const StreamArgs args
 // 11.1 -> 9.8 us, 8000 keys 15.4 -> 14.9; 4 of 512 keys 11.8 -> 10.8), from 17 rows and up to 3 slabs
 // (32/8 heads, 4088 keys 10.9 -> 10.3, 4100 keys 11.5 -> 11.2).  Elsewhere the pieces of one unit side by
 // side do better (8/8 heads, 4 sequences of 2048 keys 12.8 us against 13.6; 64/8 heads, 32773 keys, runs
-// of 17, 30.3 against 31.0; 32/8, 4 sequences, runs of 65, 83.6 against 90).
+// of 17, 30.3 against 31.0; 32/8, 4 sequences, runs of 65, 83.6 against 90), except over V^T of
+// long units, whose runs lie all over the unit's 2 MB and more (32/8 heads, d 128, 16384 keys: 1 sequence 20.5 us
+// side by side, 18.2 in turn, 4 52.6 and 48.1; 8192 keys 15.1 and 14.1; but 4 of 4096 17.2 and 17.7).
 // A run that crosses into the next unit stalls once (the flush, 1.6 us at 48
 // rows, d 128) and units get one piece more, so by unit is taken up to 2 slabs
 // and 1/16 above the even share: the draft's 16 sequences of 700 .. 1500 keys
@@ -814,7 +816,8 @@ void plan_stream(StreamArgs &a, int B, int Hkv, int d, const int *n_keys) {
         }
         if (!whole && wgs * Hkv > kStreamWGs) continue;
         for (int b = B; b < kMaxB; ++b) a.row[b].z = wgs;
-        a.by_unit = Hkv % 8 == 0 && share <= (a.T * a.G >= 32 ? 16 : a.T * a.G > 16 ? 3 : 0) ? 1 : 2;
+        const bool long_vt = a.kind == kStreamVT && nt_max >= 128;
+        a.by_unit = Hkv % 8 == 0 && (long_vt || share <= (a.T * a.G >= 32 ? 16 : a.T * a.G > 16 ? 3 : 0)) ? 1 : 2;
         a.wgs = wgs;
         a.n_wg = wgs * Hkv;
         break;
