@@ -704,7 +704,7 @@ __global__ __launch_bounds__(256) void stream_merge_kernel(const StreamArgs args
         f32x4_v v[U];
         float2 ml[U];
         #pragma unroll
-        for (int k = 0; k < U; ++k) {   // past the unit's pieces: the last one again, weighted 0
+        for (int k = 0; k < U; ++k) {   // past the unit's pieces: the last one again, not used
             const size_t at = (size_t)min(p0 + k * NG, up.np - 1) * pf;
             ml[k] = *reinterpret_cast<const float2 *>(pm + at);
             v[k] = *reinterpret_cast<const f32x4_v *>(po + at);
@@ -717,10 +717,11 @@ __global__ __launch_bounds__(256) void stream_merge_kernel(const StreamArgs args
         y *= c;
         #pragma unroll
         for (int k = 0; k < U; ++k) {
-            const float wt = p0 + k * NG < up.np ? __builtin_amdgcn_exp2f(ml[k].x - mr) : 0.f;
+            const bool in = p0 + k * NG < up.np;   // (a weight of 0 would make NaN of an infinite value)
+            const float wt = in ? __builtin_amdgcn_exp2f(ml[k].x - mr) : 0.f;
             L = fmaf(wt, ml[k].y, L);
             #pragma unroll
-            for (int e = 0; e < 4; ++e) y[e] = fmaf(wt, v[k][e], y[e]);
+            for (int e = 0; e < 4; ++e) y[e] = fmaf(wt, in ? v[k][e] : 0.f, y[e]);
         }
         M = mn;
     };

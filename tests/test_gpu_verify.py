@@ -243,3 +243,16 @@ def test_transposed_v_runs_off_line_boundaries(d, tail, pad):
         vn[b, :, length[b]:] = float("nan")
     out, lse = _run(q, kn, vn, length, "transposed_v")
     _check(q, k, v, length, out, lse)
+
+
+@pytest.mark.parametrize("d,slabs", [(64, 5), (64, 17), (128, 3), (128, 9), (128, 33)])
+def test_an_infinite_value_in_the_last_piece_stays_infinite(d, slabs):
+    # one unit of 40 query rows in pieces of a slab, merged by a second launch whose threads read the last piece
+    # again where there are fewer pieces than threads for them
+    T, G, slab = 5, 8, 8192 // d
+    n = slabs * slab
+    q, k, v = _inputs(1, T, G, 1, d, n, seed=3 * slabs + d)
+    v[:, :, n - 1 - T, 7] = float("inf")   # a key that every query sees
+    out, _ = _run(q, k, v, [n])
+    assert torch.all(torch.isposinf(out[..., 7].float()))
+    assert torch.all(torch.isfinite(out[..., :7].float())) and torch.all(torch.isfinite(out[..., 8:].float()))
